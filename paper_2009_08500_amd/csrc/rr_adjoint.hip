@@ -6,29 +6,35 @@
 //   dlogL/dtheta = sum_t psi_t dF_t/dtheta,       F_t = 1 - mean_s delta_s
 //   delta = ip(g, k) a(z, k) / I_star                               (Eq. 5)
 //
-// k_adjoint     workgroups of two wave64 over tiles of 1024 times of one
-//               parameter vector (one tile each without the profile
-//               gradient), lanes along time.  Out-of-window exposures only
-//               add their residual to logL.  For the others the subsample
-//               loop evaluates delta together with d delta/dz and
+//   k_adj_prep    the per-row constants, and for every block of 64 exposures
+//               its time bounds and the sum of its exposures' terms with
+//               F = 1, in one launch.
+//   k_adjoint     one or a few workgroups of two wave64 per parameter vector,
+//               each wave taking its share of the vector's in-transit
+//               exposures (found through the blocks' bounds, packed 64 at a
+//               time) and adding only what they change from F = 1.  The
+//               subsample loop evaluates delta together with d delta/dz and
 //               d delta/dk, and z's derivatives through the transit-centred
 //               Kepler solution (dE/dM = 1/(1 - e cos E),
 //               dE/de = sin E/(1 - e cos E)); the lens area gives
 //               da/dz = -chord and da/dk = 2 k kappa_0.  Per-lane sums are
 //               FP64 and reduced in a fixed order (butterfly within the wave,
 //               then waves in order) to one partial per workgroup.  With the
-//               profile gradient requested each workgroup runs several
-//               consecutive tiles, and a second subsample loop scatters
-//               psi-weighted lerp weights into its wave's own LDS copy of
-//               d logL / d ldw and d logL / d I_star (no two waves share an
-//               address, and one wave's LDS additions complete in program
-//               order); the copies are added in wave order and stored once
-//               per workgroup, and k_prof_seg_sum adds a vector's workgroups
-//               in order.  Every sum therefore has an order fixed by the
-//               inputs alone: the gradient is bitwise reproducible.
-//   k_adjoint_reduce   per parameter vector, the workgroup partials in a
-//               fixed order (lanes over tiles, then a butterfly) -> logL and
-//               the gradient row.
+//               profile gradient psi-weighted lerp weights are scattered
+//               into the wave's own LDS copy of d logL / d ldw (no two waves
+//               share an address, and one wave's LDS additions complete in
+//               program order); the copies are added in wave order and
+//               stored once per workgroup, and k_prof_seg_sum adds a
+//               vector's workgroups in order.  Every sum therefore has an
+//               order fixed by the inputs alone: the gradient is bitwise
+//               reproducible.
+//               Measured against the earlier form (every workgroup testing
+//               a tile of 2048 exposures and evaluating the flagged ones
+//               where they stood), 1024 walkers x 50 000 times x 5: float
+//               132 -> 61 us, FP64 with the profile gradient 414 -> 148 us.
+//   k_adjoint_reduce   per parameter vector, the workgroup partials and the
+//               blocks' sums in a fixed order (lanes, then a butterfly) ->
+//               logL and the gradient row.
 //   k_table_grad d logL / d T[pb][i][m] from the per-vector d logL / d ldw
 //               through the k-interpolation weights: chunks of vectors in
 //               parallel, each in order, then the chunks in order.
@@ -152,17 +158,6 @@ __device__ inline T wave_sum(T v) {
     return v;
 }
 
-// Workgroup (ipv, c) = blockIdx.x = ipv nparts + c handles the time tiles
-// [c tpp, (c + 1) tpp) of vector ipv (tpp = tiles per part, 1 without the
-// profile gradient).  Per tile, pass 1 adds the residuals of exposures that
-// cannot overlap the star; pass 2 runs the subsample loop of the others.
-// The LDS tables (ldw and its k-derivative) are built at the first tile with
-// in-window work.  Per-lane sums go to one partial per workgroup; with the
-// profile gradient the workgroup's LDS sums of d logL / d ldw and
-// d logL / d I_star are stored once at the end, to slot (ipv, c) of
-// seg_gw / seg_gi with flag 1 (flag 0 and nothing else if no exposure was in
-// the window), or, with seg_flag NULL (one part per vector), as the final
-// per-vector sums.
 // sum over c = 0 .. n-1, in order, of (flag(c) ? val(c) : 0), with eight
 // flags and then eight values loaded at a time (their loads are independent,
 // so a flagged sum over many parts costs n/8 memory round trips, not n)
@@ -184,33 +179,103 @@ __device__ inline double flagged_sum(int n, F flag, V val, bool* any = nullptr) 
     return s;
 }
 
+// What every row needs before the main kernel, in one launch.  Workgroups
+// [0, nrow_blocks): the per-row constants, one thread per row.  The others:
+// one wave per block of kTimeBlock exposures, its bounds (block_in_window)
+// and the log-likelihood of its exposures with F = 1, so that the main
+// kernel adds the difference of the few exposures in transit and never
+// reads the others.  A light-curve id out of range makes the block's sum NaN.
+template <bool kF32, typename R>
+__global__ __launch_bounds__(kBlock) void k_adj_prep(
+    const double* __restrict__ pv, int32_t npv, int32_t npar, double k_lo, double k_hi,
+    double k_small, PvConst* __restrict__ pvc, int32_t nrow_blocks,
+    const double* __restrict__ times, const int32_t* __restrict__ lcids, int32_t npt, LcInfo lc,
+    const R* __restrict__ obs, double inv_sig2, int32_t nblk, double* __restrict__ blk_lo,
+    double* __restrict__ blk_hi, double* __restrict__ blk_ll) {
+    if (int(blockIdx.x) < nrow_blocks) {
+        const int ipv = int(blockIdx.x) * kBlock + int(threadIdx.x);
+        if (ipv < npv)
+            pvc[ipv] = make_pv_const<kF32>(pv + int64_t(ipv) * npar, npar - 6, k_lo, k_hi, k_small);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const int b = (int(blockIdx.x) - nrow_blocks) * (kBlock / 64) + int(threadIdx.x >> 6);
+    if (b >= nblk) return;                                  // whole waves leave together
+    const int it = b * kTimeBlock + lane;
+    double lo = INFINITY, hi = -INFINITY, ll = 0.0;
+    if (it < npt) {
+        const int l = lcids ? lcids[it] : 0;
+        if (l < 0 || l >= lc.nlc) {
+            ll = NAN;
+        } else {
+            const double t = times[it], hw = 0.5 * lc.exptime[l];
+            if (is_finite(t)) { lo = t - hw; hi = t + hw; }
+            const double r = double(obs[it]) - 1.0;
+            ll = -0.5 * r * r * inv_sig2;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, off, 64));
+        hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    ll = wave_sum(ll);
+    if (lane == 0) { blk_lo[b] = lo; blk_hi[b] = hi; blk_ll[b] = ll; }
+}
+
+// Workgroup ipv nparts + c: part c of row ipv's in-window exposures.  Each of
+// its waves works on its own: it finds the row's blocks of exposures that
+// may be in a transit from the blocks' bounds, takes every (nparts waves)-th
+// of them, tests their exposures and packs the flagged ones in a ring in
+// LDS, from which it evaluates 64 at a time, one per lane (all lanes busy
+// until the wave's last batch).  The kernel is bound by that arithmetic, so
+// full batches and no work on exposures outside a transit are what count:
+// with a tile of 2048 exposures per workgroup, flagged exposures evaluated
+// where they stood, the transit filled 70 % of the lanes and three quarters
+// of the workgroups only added residuals.
+//   The LDS tables (ldw and its k-derivative) are built once per workgroup.
+// With the profile gradient the FP64 subsample loop keeps each overlapping
+// subsample's separation and area in LDS (sub_lds of them per thread;
+// exposures with more, and float, where it gained only 6 %, evaluate them a
+// second time), and the weighted lerp weights go to the wave's own copy of d logL / d ldw once the exposure's
+// residual is known; the copies are stored to slot (ipv, c) of seg_gw /
+// seg_gi with flag 1 (flag 0 and nothing else if no exposure was in the
+// window), or, with seg_flag NULL (one part per vector), as the final
+// per-vector sums.
+//   use_ring 0 (tables that leave no LDS for the ring): a block's flagged
+// exposures are evaluated where they stand.
+constexpr int kRing = 128;                    // exposures; at most 127 are held
 template <typename R, int NPBT, bool kProf>
 __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
     const double* __restrict__ times, const int32_t* __restrict__ lcids,
     int32_t npt, LcInfo lc, const double* __restrict__ pv, int32_t npar,
     const PvConst* __restrict__ pvc, GridDev g, const R* __restrict__ T,
     const double* __restrict__ inv_istar, const R* __restrict__ obs,
-    double inv_sig2, int32_t ntiles, int32_t nparts, int32_t tpp, int32_t want_grad,
+    double inv_sig2, int32_t nblk, const double* __restrict__ blk_lo,
+    const double* __restrict__ blk_hi, int32_t nparts, int32_t want_grad,
     const double* __restrict__ wprof, double* __restrict__ partials,
     double* __restrict__ seg_gw, double* __restrict__ seg_gi, int32_t* __restrict__ seg_flag,
-    int32_t rows_per_vector) {
+    int32_t rows_per_vector, int32_t use_ring, int32_t sub_lds) {
     extern __shared__ unsigned char smem_raw[];
-    constexpr int kJ = adj_times_per_thread(kProf, sizeof(R) == 8);   // times per thread
-    constexpr int kTile = kAdjBlock * kJ;
     constexpr int kWaves = kAdjBlock / 64;
     const int npb = g.npb, ng = g.ng;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     R* ldw = reinterpret_cast<R*>(smem_raw);                    // [npb][ng]
     R* dTk = ldw + npb * ng;                                    // [npb][ng]
-    // per-wave copies of d logL / d ldw [kWaves][npb][ng] and
-    // d logL / d I_star [kWaves][npb] (profile instantiation only)
+    // per-wave d logL / d ldw [kWaves][npb][ng] and d logL / d I_star
+    // [kWaves][npb] (profile instantiation only), then each thread's
+    // subsamples [sub_lds][2][kAdjBlock] and the waves' rings
     double* gw_all = reinterpret_cast<double*>(
         smem_raw + ((2 * sizeof(R) * npb * ng + 7) / 8) * 8);
-    double* gi_all = gw_all + kWaves * npb * ng;
     double* gw = gw_all + wave * npb * ng;                      // this wave's copy
-    double* gi = gi_all + wave * npb;
+    double* gi_all = gw_all + kWaves * npb * ng;                // [kWaves][npb]
+    unsigned char* rest = reinterpret_cast<unsigned char*>(
+        kProf ? gi_all + kWaves * npb : gw_all);
+    R* sub = reinterpret_cast<R*>(rest) + tid;
+    int32_t* ring = reinterpret_cast<int32_t*>(rest + (kProf ? 2 * sizeof(R) * sub_lds * kAdjBlock : 0)) +
+                    wave * kRing;
     __shared__ double red[kWaves][kNq + NPBT];
-    __shared__ int wave_any[2][kWaves];                         // by tile parity
+    __shared__ int wave_any[kWaves];
     static_assert(sizeof(red) + sizeof(wave_any) <= kAdjStaticLds,
                   "static LDS must fit the reserve the host budget assumes");
 
@@ -237,96 +302,107 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
 
     double ll = 0.0;
     double ga[6] = {0, 0, 0, 0, 0, 0};
-    double gk[NPBT];
+    double gk[NPBT], gi[kProf ? NPBT : 1];
 #pragma unroll
-    for (int q = 0; q < NPBT; ++q) gk[q] = 0.0;
-    bool ready = false;                  // LDS tables built (uniform)
+    for (int q = 0; q < NPBT; ++q) {
+        gk[q] = 0.0;
+        if (kProf) gi[q] = 0.0;
+    }
 
-    // without the profile gradient: exactly one tile, tile c
-    const int tile0 = kProf ? c * tpp : c;
-    const int tile_end = kProf ? min(ntiles, (c + 1) * tpp) : c + 1;
-    for (int tile = tile0; tile < tile_end; ++tile) {
-        const int t_base = tile * kTile + tid;
-        // Pass 1: residuals of exposures that cannot overlap the star.
-        uint32_t todo = 0;
-        const int tfirst = tile * kTile;
-        if (!lcids && tfirst + kTile <= npt) {
-            // whole tile in range, one light curve (see forward_block)
-            double tv[kJ], ov[kJ];
-#pragma unroll
-            for (int j = 0; j < kJ; ++j) {
-                tv[j] = times[tfirst + tid + j * kAdjBlock];
-                ov[j] = double(obs[tfirst + tid + j * kAdjBlock]);
+    for (int idx = tid; idx < npb * ng; idx += kAdjBlock) {
+        const int pb = idx / ng, m = idx - pb * ng;
+        const double u = (pv[int64_t(ipv) * npar + 6 + pb] - g.k0) / g.dk;
+        int ik = int(floor(u));
+        ik = ik < 0 ? 0 : (ik > g.nk - 2 ? g.nk - 2 : ik);
+        const R ak = R(u - ik);
+        // the shared table's two rows, or the vector's own copies
+        const R* t0r = rows_per_vector ? T + (int64_t(ipv) * npb + pb) * 2 * ng
+                                       : T + (int64_t(pb) * g.nk + ik) * ng;
+        ldw[idx] = (R(1) - ak) * t0r[m] + ak * t0r[ng + m];
+        dTk[idx] = (t0r[ng + m] - t0r[m]) * R(g.inv_dk);
+    }
+    if (kProf)
+        for (int idx = tid; idx < kWaves * npb * ng; idx += kAdjBlock) gw_all[idx] = 0.0;
+    __syncthreads();
+
+    const OrbitR<R> orb(p);
+    const DerivR<R> dv(make_pv_deriv(p, pv[int64_t(ipv) * npar + 3]));
+    const R gscale = R(g.gscale);
+    const R invP = R(p.invP);
+
+    // The wave's blocks: of the row's hit blocks, in block order, numbers
+    // skip, skip + nw, skip + 2 nw, ... (wave-uniform).
+    const int nw = nparts * kWaves;
+    int skip = __builtin_amdgcn_readfirstlane(c * kWaves + wave), scan = 0, at = 0;
+    uint64_t hits = 0;
+    auto next_block = [&]() -> int {
+        for (;;) {
+            while (hits == 0) {
+                if (scan >= nblk) return -1;
+                const int b = scan + lane;
+                hits = __ballot(b < nblk && block_in_window(blk_lo[b < nblk ? b : 0],
+                                                            blk_hi[b < nblk ? b : 0], p));
+                at = scan;
+                scan += 64;
             }
-            const double hw = 0.5 * lc.exptime[0] * p.invP;
-            const double c0 = -p.t0 * p.invP - (p.flo - hw);
-            const double wn = p.wn + 2.0 * hw;
-#pragma unroll
-            for (int j = 0; j < kJ; ++j) {
-                const double gph = fma(tv[j], p.invP, c0);
-                if (gph - floor(gph) < wn) {
-                    todo |= 1u << j;
-                } else {
-                    const double r = ov[j] - 1.0;
-                    ll -= 0.5 * r * r * inv_sig2;
-                }
+            const int bit = __builtin_ctzll(hits);
+            hits &= hits - 1;
+            if (skip == 0) {
+                skip = nw - 1;
+                return at + bit;
             }
-        } else {
-            for (int j = 0; j < kJ; ++j) {
-                const int it = t_base + j * kAdjBlock;
-                if (it >= npt) continue;
-                const int l = lcids ? lcids[it] : 0;
-                if (l < 0 || l >= lc.nlc) { ll = NAN; continue; }
-                if (in_phase_window((times[it] - p.t0) * p.invP, p, 0.5 * lc.exptime[l] * p.invP)) {
-                    todo |= 1u << j;
-                } else {
-                    const double r = double(obs[it]) - 1.0;
-                    ll -= 0.5 * r * r * inv_sig2;
-                }
-            }
+            --skip;
         }
-        // wave_any is double-buffered by tile parity: a wave that runs ahead
-        // to the next tile writes the other half while slower waves read
-        const int par = tile & 1;
-        const int wany = __any(todo != 0);
-        if (lane == 0) wave_any[par][wave] = wany;
-        __syncthreads();
-        bool any = false;
-#pragma unroll
-        for (int w = 0; w < kAdjBlock / 64; ++w) any |= wave_any[par][w] != 0;
-        if (!any) continue;
+    };
 
-        if (!ready) {
-            for (int idx = tid; idx < npb * ng; idx += kAdjBlock) {
-                const int pb = idx / ng, m = idx - pb * ng;
-                const double u = (pv[int64_t(ipv) * npar + 6 + pb] - g.k0) / g.dk;
-                int ik = int(floor(u));
-                ik = ik < 0 ? 0 : (ik > g.nk - 2 ? g.nk - 2 : ik);
-                const R ak = R(u - ik);
-                // the shared table's two rows, or the vector's own copies
-                const R* t0r = rows_per_vector ? T + (int64_t(ipv) * npb + pb) * 2 * ng
-                                               : T + (int64_t(pb) * g.nk + ik) * ng;
-                ldw[idx] = (R(1) - ak) * t0r[m] + ak * t0r[ng + m];
-                dTk[idx] = (t0r[ng + m] - t0r[m]) * R(g.inv_dk);
+    bool any = false;                    // an exposure was in the window (uniform)
+    int head = 0, cnt = 0;
+    int blk = next_block();
+    double tn = 0.0;                     // the next block's times and ids, loaded ahead
+    int ln = -1;
+    auto load_block = [&]() {
+        const int it = blk * kTimeBlock + lane;
+        const bool in = blk >= 0 && it < npt;
+        tn = in ? times[it] : 0.0;
+        ln = in ? (lcids ? lcids[it] : 0) : -1;
+    };
+    load_block();
+    for (;;) {
+        int it = -1;                     // this lane's exposure
+        while (blk >= 0 && cnt < 64) {
+            const int cand = blk * kTimeBlock + lane;
+            const double t = tn;
+            const int l = ln;
+            blk = next_block();
+            load_block();
+            const bool in = l >= 0 && l < lc.nlc &&
+                            in_phase_window((t - p.t0) * p.invP, p,
+                                            0.5 * lc.exptime[l >= 0 && l < lc.nlc ? l : 0] * p.invP);
+            const uint64_t m = __ballot(in);
+            if (!use_ring) {
+                if (m == 0) continue;
+                it = in ? cand : -1;
+                any = true;
+                break;
             }
-            if (kProf) {
-                for (int idx = tid; idx < kWaves * npb * ng; idx += kAdjBlock) gw_all[idx] = 0.0;
-                if (tid < kWaves * npb) gi_all[tid] = 0.0;
-            }
-            __syncthreads();
-            ready = true;
+            if (in) ring[(head + cnt + __popcll(m & __lanemask_lt())) & (kRing - 1)] = cand;
+            cnt += __popcll(m);
         }
-
-        const OrbitR<R> orb(p);
-        const DerivR<R> dv(make_pv_deriv(p, pv[int64_t(ipv) * npar + 3]));
-        const R gscale = R(g.gscale);
-        const R invP = R(p.invP);
-
-        // Pass 2: the exposures that may overlap the star.
-        while (todo) {
-            const int j = __builtin_ctz(todo);
-            todo &= todo - 1;
-            const int it = t_base + j * kAdjBlock;
+        if (use_ring) {
+            if (cnt == 0) break;
+            any = true;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int n = cnt < 64 ? cnt : 64;
+            it = lane < n ? ring[(head + lane) & (kRing - 1)] : -1;
+            head += n;
+            cnt -= n;
+            __builtin_amdgcn_wave_barrier();
+        } else if (!__any(it >= 0)) {
+            break;
+        }
+        if (it >= 0) {
             const int l = lcids ? lcids[it] : 0;
             const int pb = lc.pb[l];
             const int nss = lc.nss[l];
@@ -343,7 +419,9 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
             R gt[6] = {0, 0, 0, 0, 0, 0};
             R gkt = R(0);
             const double inv_nss = 1.0 / nss;
+            const bool keep = kProf && sizeof(R) == 8 && nss <= sub_lds;
             for (int s = 0; s < nss; ++s) {
+                if (keep) sub[(2 * s + 1) * kAdjBlock] = R(0);     // no overlap
                 const double x = (t + ex * ((s + 0.5) * inv_nss - 0.5)) - p.t0;
                 const double u = x * p.invP;
                 if (!in_phase_window(u, p, 0.0)) continue;
@@ -359,6 +437,10 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
                 const R ip = (R(1) - al) * lw[m] + al * lw[m + 1];
                 R Az, Ak;
                 const R A = lens_area_grad<R>(k, z, &Az, &Ak);
+                if (keep) {
+                    sub[2 * s * kAdjBlock] = z;
+                    sub[(2 * s + 1) * kAdjBlock] = A;
+                }
                 acc += ip * A * istar_inv;
                 if (want_grad) {
                     const R slope = (lw[m + 1] - lw[m]) * gscale;
@@ -370,10 +452,13 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
                     for (int q = 0; q < 6; ++q) gt[q] += ddz * dz[q];
                 }
             }
-            // residual in FP64: d - F = (d - 1) + mean delta
+            // residual in FP64: d - F = (d - 1) + mean delta, and the change of
+            // its square from F = 1 (in the block sums); a residual that is not
+            // finite has made the block sum infinite or NaN already
             const double mean_delta = double(acc) / nss;
-            const double r = (double(obs[it]) - 1.0) + mean_delta;
-            ll -= 0.5 * r * r * inv_sig2;
+            const double r0 = double(obs[it]) - 1.0;
+            const double r = r0 + mean_delta;
+            if (is_finite(r0)) ll -= 0.5 * mean_delta * (r0 + r) * inv_sig2;
             const double wgt = -(r * inv_sig2) / nss;       // dlogL / d delta_s
             if (want_grad) {
 #pragma unroll
@@ -384,54 +469,43 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
             if (kProf) {
                 // psi-weighted lerp weights of each overlapping subsample
                 const double cw = wgt * (wprof ? wprof[ipv] : 1.0);
+                double git = 0.0;
                 for (int s = 0; s < nss; ++s) {
-                    const double x = (t + ex * ((s + 0.5) * inv_nss - 0.5)) - p.t0;
-                    const double u = x * p.invP;
-                    if (!in_phase_window(u, p, 0.0)) continue;
-                    const double dt = x - p.P * rint(u);
-                    bool front;
-                    const R z = separation<R>(R(dt), orb, &front);
-                    if (!front || !(z < onepk)) continue;
+                    R z, area;
+                    if (keep) {
+                        area = sub[(2 * s + 1) * kAdjBlock];
+                        if (area == R(0)) continue;
+                        z = sub[2 * s * kAdjBlock];
+                    } else {
+                        const double x = (t + ex * ((s + 0.5) * inv_nss - 0.5)) - p.t0;
+                        const double u = x * p.invP;
+                        if (!in_phase_window(u, p, 0.0)) continue;
+                        const double dt = x - p.P * rint(u);
+                        bool front;
+                        z = separation<R>(R(dt), orb, &front);
+                        if (!front || !(z < onepk)) continue;
+                        area = lens_area<R>(R(1), k, z);
+                    }
                     const R v = z * inv1pk * gscale;
                     int m = int(v);
                     m = m > ng - 2 ? ng - 2 : m;
                     const double al = double(v - R(m));
-                    const double A = double(lens_area<R>(R(1), k, z)) * double(istar_inv);
+                    const double A = double(area) * double(istar_inv);
                     const double cc = cw * A;
                     atomicAdd(&gw[pb * ng + m], (1.0 - al) * cc);
                     atomicAdd(&gw[pb * ng + m + 1], al * cc);
                     const double ip = (1.0 - al) * double(lw[m]) + al * double(lw[m + 1]);
-                    atomicAdd(&gi[pb], -cw * ip * A * double(istar_inv));
+                    git -= cw * ip * A * double(istar_inv);
                 }
-            }
-        }
-    }
-
-    if (kProf) {
-        __syncthreads();                 // every wave's LDS additions done
-        // the waves' copies added in wave order
-        auto wsum = [&](const double* base, int stride, int idx) {
-            double v = base[idx];
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) v += base[w * stride + idx];
-            return v;
-        };
-        double* out = seg_gw + slot * npb * ng;
-        if (seg_flag) {
-            if (tid == 0) seg_flag[slot] = ready ? 1 : 0;
-            if (ready) {
-                for (int idx = tid; idx < npb * ng; idx += kAdjBlock)
-                    out[idx] = wsum(gw_all, npb * ng, idx);
-                if (tid < npb) seg_gi[slot * npb + tid] = wsum(gi_all, npb, tid);
+                for (int q = 0; q < NPBT; ++q) gi[q] += (q == pb) ? git : 0.0;
             }
-        } else {
-            for (int idx = tid; idx < npb * ng; idx += kAdjBlock)
-                out[idx] = ready ? wsum(gw_all, npb * ng, idx) : 0.0;
-            if (tid < npb) seg_gi[slot * npb + tid] = ready ? wsum(gi_all, npb, tid) : 0.0;
         }
     }
 
-    // fixed-order reduction of the per-lane sums
+    // fixed-order reduction of the per-lane sums: butterfly within the wave,
+    // then the waves in order
+    if (lane == 0) wave_any[wave] = any;
     double vals[kNq + NPBT];
     vals[0] = ll;
 #pragma unroll
@@ -443,11 +517,35 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(
         const double v = wave_sum(vals[q]);
         if (lane == 0) red[wave][q] = v;
     }
-    __syncthreads();
+    if (kProf) {
+#pragma unroll
+        for (int q = 0; q < NPBT; ++q) {
+            const double v = wave_sum(gi[q]);
+            if (lane == 0 && q < npb) gi_all[wave * npb + q] = v;
+        }
+    }
+    __syncthreads();                     // also: every wave's LDS additions done
     if (tid < nq) {
         double sum = 0.0;
-        for (int w = 0; w < kAdjBlock / 64; ++w) sum += red[w][tid];
+        for (int w = 0; w < kWaves; ++w) sum += red[w][tid];
         part[tid] = sum;
+    }
+    if (kProf) {
+        bool ready = false;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) ready = ready || wave_any[w] != 0;
+        if (seg_flag && tid == 0) seg_flag[slot] = ready ? 1 : 0;
+        if (seg_flag && !ready) return;
+        // the waves' copies added in wave order
+        auto wsum = [&](const double* base, int stride, int idx) {
+            double v = base[idx];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) v += base[w * stride + idx];
+            return v;
+        };
+        double* out = seg_gw + slot * npb * ng;
+        for (int idx = tid; idx < npb * ng; idx += kAdjBlock) out[idx] = wsum(gw_all, npb * ng, idx);
+        if (tid < npb) seg_gi[slot * npb + tid] = wsum(gi_all, npb, tid);
     }
 }
 
@@ -479,10 +577,12 @@ __global__ void k_fill(double* __restrict__ p, int64_t n) {
     if (i < n) p[i] = 0.0;
 }
 
-// One wave per (row, quantity): lane l sums the partials of tiles l, l + 64,
-// ... in order, then a fixed butterfly across the lanes.
+// One wave per (row, quantity): lane l sums the partials of parts l, l + 64,
+// ... in order, then a fixed butterfly across the lanes; logL adds the sum
+// over every exposure with F = 1, its time blocks summed the same way.
 __global__ void k_adjoint_reduce(const double* __restrict__ partials, int32_t npv,
-                                 int32_t ntiles, int32_t npb, double* __restrict__ logl,
+                                 int32_t nparts, int32_t npb, int32_t nblk,
+                                 const double* __restrict__ blk_ll, double* __restrict__ logl,
                                  double* __restrict__ grad) {
     const int nq = kNq + npb;
     const int64_t wv = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
@@ -490,7 +590,9 @@ __global__ void k_adjoint_reduce(const double* __restrict__ partials, int32_t np
     if (wv >= int64_t(npv) * nq) return;                 // whole waves leave together
     const int ipv = int(wv / nq), q = int(wv - int64_t(ipv) * nq);
     double s = 0.0;
-    for (int tl = lane; tl < ntiles; tl += 64) s += partials[(int64_t(ipv) * ntiles + tl) * nq + q];
+    for (int c = lane; c < nparts; c += 64) s += partials[(int64_t(ipv) * nparts + c) * nq + q];
+    if (q == 0 && logl)
+        for (int b = lane; b < nblk; b += 64) s += blk_ll[b];
     s = wave_sum(s);
     if (lane != 0) return;
     if (q == 0) {
@@ -813,9 +915,10 @@ void launch_adjoint_t(const AdjointArgs& A, size_t lds, hipStream_t s, const Ker
     launch_timed(k_adjoint<R, NPBT, kProf>, dim3(unsigned(int64_t(A.nparts) * A.npv)),
                  dim3(kAdjBlock), lds, s, ev.before, ev.after, A.times, A.lcids, A.npt, *A.lc,
                  A.pv, A.npar, A.pvc, A.g, static_cast<const R*>(A.T), A.inv_istar,
-                 static_cast<const R*>(A.obs), A.inv_sig2, A.ntiles, A.nparts, A.tpp,
+                 static_cast<const R*>(A.obs), A.inv_sig2, A.nblk, A.blk_lo, A.blk_hi, A.nparts,
                  A.want_grad, A.wprof, A.partials, one ? A.gldw_pv : A.seg_gw,
-                 one ? A.gist_pv : A.seg_gi, one ? nullptr : A.seg_flag, A.rows_per_vector);
+                 one ? A.gist_pv : A.seg_gi, one ? nullptr : A.seg_flag, A.rows_per_vector,
+                 A.use_ring, A.sub_lds);
 }
 
 template <typename R>
@@ -846,8 +949,44 @@ size_t adjoint_lds_bytes(int32_t precision, int32_t npb, int32_t ng, bool prof) 
     return tables + sizeof(double) * (kAdjBlock / 64) * (size_t(npb) * ng + npb);
 }
 
-hipError_t launch_adjoint(const AdjointArgs& A, int32_t precision, hipStream_t s) {
-    const size_t lds = adjoint_lds_bytes(precision, A.g.npb, A.g.ng, A.want_prof != 0);
+size_t adjoint_plan_lds(int32_t precision, size_t lds_max, AdjointArgs* A) {
+    const size_t elt = precision == RR_FP64 ? sizeof(double) : sizeof(float);
+    size_t lds = adjoint_lds_bytes(precision, A->g.npb, A->g.ng, A->want_prof != 0);
+    const size_t ring = sizeof(int32_t) * kRing * (kAdjBlock / 64);
+    A->use_ring = lds + ring + kAdjStaticLds <= lds_max ? 1 : 0;
+    lds += A->use_ring ? ring : 0;
+    A->sub_lds = 0;
+    if (A->want_prof && precision == RR_FP64) {
+        // as many subsamples as the largest exposure with at most kSubLds has
+        for (int l = 0; l < A->lc->nlc; ++l)
+            if (A->lc->nss[l] <= kSubLds) A->sub_lds = std::max(A->sub_lds, A->lc->nss[l]);
+        const size_t per = 2 * elt * kAdjBlock;             // one subsample of every thread
+        const size_t left = lds + kAdjStaticLds < lds_max ? lds_max - lds - kAdjStaticLds : 0;
+        A->sub_lds = int32_t(std::min<size_t>(size_t(A->sub_lds), left / per));
+        lds += size_t(A->sub_lds) * per;
+    }
+    return lds;
+}
+
+template <typename R>
+void launch_prep_r(const AdjointArgs& A, double k_lo, double k_hi, double k_small, hipStream_t s) {
+    const unsigned rows = nblocks(A.npv);
+    const unsigned tb = unsigned((A.nblk + kBlock / 64 - 1) / (kBlock / 64));
+    hipLaunchKernelGGL((k_adj_prep<sizeof(R) == 4, R>), dim3(rows + tb), dim3(kBlock), 0, s, A.pv,
+                       A.npv, A.npar, k_lo, k_hi, k_small, const_cast<PvConst*>(A.pvc),
+                       int32_t(rows), A.times, A.lcids, A.npt, *A.lc,
+                       static_cast<const R*>(A.obs), A.inv_sig2, A.nblk, A.blk_lo, A.blk_hi,
+                       A.blk_ll);
+}
+
+hipError_t launch_adjoint_prep(const AdjointArgs& A, int32_t precision, double k_lo, double k_hi,
+                               double k_small, hipStream_t s) {
+    if (precision == RR_FP64) launch_prep_r<double>(A, k_lo, k_hi, k_small, s);
+    else launch_prep_r<float>(A, k_lo, k_hi, k_small, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_adjoint(const AdjointArgs& A, size_t lds, int32_t precision, hipStream_t s) {
     const KernelEvents ev = kernel_events();
     if (precision == RR_FP64) launch_adjoint_r<double>(A, lds, s, ev);
     else launch_adjoint_r<float>(A, lds, s, ev);
@@ -860,8 +999,8 @@ hipError_t launch_adjoint(const AdjointArgs& A, int32_t precision, hipStream_t s
                            nw, A.g.npb, A.gldw_pv, A.gist_pv);
     }
     hipLaunchKernelGGL(k_adjoint_reduce, dim3(nblocks(int64_t(A.npv) * (kNq + A.g.npb) * 64)),
-                       dim3(kBlock), 0, s, A.partials, A.npv, A.nparts, A.g.npb, A.logl,
-                       A.grad);
+                       dim3(kBlock), 0, s, A.partials, A.npv, A.nparts, A.g.npb, A.nblk,
+                       A.blk_ll, A.logl, A.grad);
     return hipGetLastError();
 }
 

@@ -10,7 +10,7 @@
 #include <string>
 #include <vector>
 
-#include "rr_internal.h"
+#include "rr_device.h"
 
 namespace rr {
 
@@ -141,9 +141,7 @@ int check_eval_args(const rr_tables* t, const double* times_d,
         if (!times_d) return einval("times is NULL");
         if (!pv_d) return einval("pv is NULL");
     }
-    const int64_t ntiles = (int64_t(npt) + adj_tile(true, false) - 1) /
-                           adj_tile(true, false);            // the smaller tiles
-    if (ntiles * npv * kAdjBlock >= (int64_t(1) << 32) ||
+    if ((int64_t(npt) + 1023) / 1024 * npv * kAdjBlock >= (int64_t(1) << 32) ||
         ((int64_t(npt) + 4 * kFwdBlock - 1) / (4 * kFwdBlock)) * npv * kFwdBlock >=
             (int64_t(1) << 32))                  // the smallest forward tile (J = 4)
         return elimit("npv * npt too large for one launch");
@@ -773,28 +771,31 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
         return RR_OK;
     }
     const bool prof = grad_prof_d != nullptr || grad_istar_d != nullptr;
-    const int32_t tile = adj_tile(prof, precision == RR_FP64);
-    const int32_t ntiles = npt > 0 ? (npt + tile - 1) / tile : 1;
     const int32_t nq = 7 + t->npb;
     const GridDev g = grid_dev(t);
-    // With the profile gradient each workgroup runs tpp consecutive tiles of
-    // one vector: enough workgroups to fill the chip (~16384), at most 256
-    // MiB of per-workgroup profile partials.  Without it, one tile each.
-    int64_t nseg = ntiles;
-    int32_t tpp = 1;
+    const int32_t nblk = int32_t((int64_t(npt) + kTimeBlock - 1) / kTimeBlock);
+    // Workgroups per vector (of two waves): as many waves as the kernel's
+    // registers let the chip hold at once -- 4 per SIMD in float without the
+    // profile gradient, else 2 -- since more parts only cost each row more
+    // half-filled last batches (1024 walkers x 50 000 x 5, us per call at
+    // 2048 / 4096 / 8192 waves: float 92 / 81 / 107, FP64 152 / 198 / 231,
+    // FP64 with the profile gradient 632 / 693 / 749); each wave with at
+    // least 16 time blocks to look through, and with the profile gradient at
+    // most 256 MiB of per-workgroup partials.
+    const int64_t waves = !prof && precision == RR_MIXED ? 4096 : 2048;
+    int64_t nseg = (waves + 2 * int64_t(npv) - 1) / (2 * int64_t(npv));
+    nseg = std::min<int64_t>(nseg, (int64_t(nblk) + 31) / 32);
     if (prof) {
         const size_t row_bytes = sizeof(double) * size_t(t->npb) * (size_t(g.ng) + 1);
-        int64_t want = std::min<int64_t>(ntiles, (16384 + npv - 1) / npv);
-        want = std::min<int64_t>(want, std::max<int64_t>(
-                                           1, int64_t((size_t(256) << 20) / (row_bytes * npv))));
-        tpp = int32_t((ntiles + want - 1) / std::max<int64_t>(1, want));
-        nseg = (ntiles + tpp - 1) / tpp;
+        nseg = std::min<int64_t>(nseg, int64_t((size_t(256) << 20) / (row_bytes * npv)));
     }
+    nseg = std::max<int64_t>(nseg, 1);
     // one stream-ordered allocation for every temporary
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) / 256 * 256; return o; };
     const size_t o_pvc = take(sizeof(PvConst) * size_t(npv));
     const size_t o_part = take(sizeof(double) * size_t(npv) * nseg * nq);
+    const size_t o_blk = take(sizeof(double) * 3 * size_t(nblk));
     const size_t o_gldw = prof ? take(sizeof(double) * size_t(npv) * t->npb * g.ng) : 0;
     const size_t o_gist = prof ? take(sizeof(double) * size_t(npv) * t->npb) : 0;
     // shared-profile chain (table gradient) or per-vector LD temporaries
@@ -843,20 +844,21 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
         A.T = base + o_rows;
         A.inv_istar = reinterpret_cast<double*>(base + o_iisr);
     }
-    A.ntiles = ntiles; A.want_grad = grad_d != nullptr; A.want_prof = prof; A.wprof = wprof_d;
+    A.nblk = nblk;
+    A.blk_lo = reinterpret_cast<double*>(base + o_blk);
+    A.blk_hi = A.blk_lo + nblk;
+    A.blk_ll = A.blk_hi + nblk;
+    A.want_grad = grad_d != nullptr; A.want_prof = prof; A.wprof = wprof_d;
     A.partials = reinterpret_cast<double*>(base + o_part);
     A.gldw_pv = prof ? reinterpret_cast<double*>(base + o_gldw) : nullptr;
     A.gist_pv = prof ? reinterpret_cast<double*>(base + o_gist) : nullptr;
     A.nparts = int32_t(nseg);
-    A.tpp = tpp;
     A.seg_gw = segs ? reinterpret_cast<double*>(base + o_sgw) : nullptr;
     A.seg_gi = segs ? reinterpret_cast<double*>(base + o_sgi) : nullptr;
     A.seg_flag = segs ? reinterpret_cast<int32_t*>(base + o_sfl) : nullptr;
     A.logl = logl_d; A.grad = grad_d;
-    e = sp ? launch_pv_setup_k(pv_d, npv, npar, t->grid.k0, t->grid.k1,
-                               const_cast<PvConst*>(A.pvc), precision, stream, k_small)
-           : launch_pv_setup(t, pv_d, npv, npar, const_cast<PvConst*>(A.pvc), precision,
-                             stream);
+    const size_t lds = adjoint_plan_lds(precision, t->lds_max, &A);
+    e = launch_adjoint_prep(A, precision, t->grid.k0, t->grid.k1, sp ? k_small : 0.0, stream);
     if (e == hipSuccess && sp)
         e = launch_small_planet_adj_rows(t, pv_d, npv, npar, k_small, precision, base + o_rows,
                                          reinterpret_cast<double*>(base + o_iisr), stream);
@@ -868,7 +870,7 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
                          reinterpret_cast<int32_t*>(base + o_ikr),
                          reinterpret_cast<int32_t*>(base + o_perm), base + o_rows, stream,
                          precision == RR_MIXED);     // the rows rr_evaluate_ld evaluates
-    if (e == hipSuccess) e = launch_adjoint(A, precision, stream);
+    if (e == hipSuccess) e = launch_adjoint(A, lds, precision, stream);
     if (e == hipSuccess && prof && per_row)
         e = launch_pv_prof_grad(t, A, reinterpret_cast<const int32_t*>(base + o_ikr),
                                 reinterpret_cast<const int32_t*>(base + o_perm),

@@ -446,6 +446,25 @@ __device__ inline bool in_phase_window(double u, const PvConst& p, double hw_pha
     return (g - floor(g)) < p.wn + 2.0 * hw_phase;
 }
 
+// Bounds of a block of 64 consecutive exposures: [lo, hi] holds every
+// subsample time of the block's finite exposures (half an exposure on each
+// side of the mid-times), lo > hi if it has none.  A row skips the blocks
+// whose interval misses its transit windows; nothing is assumed about the
+// order of the times (an unsorted block is merely wide).
+constexpr int kTimeBlock = 64;
+
+// Can any exposure of a block with bounds [lo, hi] pass in_phase_window for
+// row p?  Conservative: the window is widened by a bound on the rounding of
+// the phases (a few 1e-16 of t / P and t0 / P), so a block that is skipped
+// holds no exposure in the window.
+__device__ inline bool block_in_window(double lo, double hi, const PvConst& p) {
+    const double a = -p.t0 * p.invP;
+    const double glo = fma(lo, p.invP, a) - p.flo, ghi = fma(hi, p.invP, a) - p.flo;
+    const double m = 1e-12 + 4e-15 * (fabs(a) + fabs(lo * p.invP) + fabs(hi * p.invP));
+    const double f = floor(glo - m);
+    return lo <= hi && !((glo - m) - f >= p.wn + 2.0 * m && (ghi + m) - f < 1.0);
+}
+
 // Per-vector LD: a tile of 16 consecutive rows in k-row order goes to the
 // matrix cores when its rows span at most kMfmaMaxRuns k-rows (each W value
 // is then read once for the tile), else to the per-row kernels.  The

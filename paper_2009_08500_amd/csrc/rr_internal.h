@@ -30,11 +30,9 @@ constexpr int kFwdBlock = 64;
 constexpr int kFwdTile = kFwdBlock * kTimesPerThread;
 constexpr int kSplitRows = 4;       // rows per streaming workgroup of the split launch
 // Log-likelihood kernel: two wave64 per workgroup share the LDS tables.
-// Times per thread: 16, except 8 with the LD-profile gradient in mixed
-// precision (measured fastest for each).
 constexpr int kAdjBlock = 128;
-constexpr int adj_times_per_thread(bool prof, bool f64) { return prof && !f64 ? 8 : 16; }
-constexpr int adj_tile(bool prof, bool f64) { return kAdjBlock * adj_times_per_thread(prof, f64); }
+// Subsamples per exposure whose terms the profile gradient keeps in LDS.
+constexpr int kSubLds = 10;
 constexpr int kMinLdsBytes = 64 * 1024;   // LDS a workgroup may use on any
                                           // device (the budget used if the
                                           // device does not report its own)
@@ -138,15 +136,19 @@ struct AdjointArgs {
     const double* inv_istar;
     const void* obs;          // double (RR_FP64) or float (RR_MIXED)
     double inv_sig2;
-    int32_t ntiles, want_grad, want_prof;
+    int32_t want_grad, want_prof;
+    // blocks of kTimeBlock exposures: bounds, and the log-likelihood of their
+    // exposures with F = 1 ([nblk] each)
+    int32_t nblk;
+    double *blk_lo, *blk_hi, *blk_ll;
+    int32_t use_ring, sub_lds;   // adjoint_plan_lds
     const double* wprof;      // per-vector weights of the profile gradient
     double* partials;         // [npv * nparts][7 + npb]
     double* gldw_pv;          // [npv][npb][ng]
     double* gist_pv;          // [npv][npb]
     int32_t rows_per_vector;  // 1: T holds each vector's own two rows [npv][npb][2][ng]
                               // and inv_istar is [npv][npb] (per-vector LD)
-    int32_t nparts;           // workgroups per vector (ntiles without the profile gradient)
-    int32_t tpp;              // tiles per workgroup
+    int32_t nparts;           // workgroups per vector
     double* seg_gw;           // [npv][nparts][npb][ng] (nparts > 1)
     double* seg_gi;           // [npv][nparts][npb]
     int32_t* seg_flag;        // [npv][nparts]
@@ -234,14 +236,20 @@ hipError_t launch_pv_setup(const rr_tables* t, const double* pv, int32_t npv,
 hipError_t launch_pv_setup_k(const double* pv, int32_t npv, int32_t npar, double k_lo,
                              double k_hi, PvConst* pvc, int32_t precision, hipStream_t s,
                              double k_small = 0.0);
-// Dynamic LDS of one log-likelihood workgroup: the k-interpolated LD
-// vectors and their k-derivatives, plus (prof) each wave's copy of
-// d logL / d ldw and d logL / d I_star.
+// The dynamic LDS one log-likelihood workgroup cannot do without: the
+// k-interpolated LD vectors and their k-derivatives, plus (prof) each wave's
+// copy of d logL / d ldw and d logL / d I_star.
 size_t adjoint_lds_bytes(int32_t precision, int32_t npb, int32_t ng, bool prof);
+// What the launch asks for: those, and as far as they fit the exposure rings
+// and (prof) the subsamples' terms; sets use_ring and sub_lds.
+size_t adjoint_plan_lds(int32_t precision, size_t lds_max, AdjointArgs* a);
 // What the log-likelihood kernel declares in LDS statically (an upper
 // bound): the dynamic part must fit in lds_max less this.
 constexpr size_t kAdjStaticLds = 512;
-hipError_t launch_adjoint(const AdjointArgs& a, int32_t precision, hipStream_t s);
+// Per-row constants (launch_pv_setup_k's), time-block bounds and sums.
+hipError_t launch_adjoint_prep(const AdjointArgs& a, int32_t precision, double k_lo, double k_hi,
+                               double k_small, hipStream_t s);
+hipError_t launch_adjoint(const AdjointArgs& a, size_t lds, int32_t precision, hipStream_t s);
 // Temporaries of the profile gradient.
 struct ProfGradScratch {
     int32_t* kidx;        // [npv][npb]
