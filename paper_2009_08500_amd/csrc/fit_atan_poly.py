@@ -70,7 +70,7 @@ def header_coefficients(path):
     fl = [float(x) for x in re.findall(r"float p = ([-+]?\d\.\d+e[-+]\d+)f;", fpart)]
     fl += [float(sg + x) for sg, x in re.findall(r"p = p \* t ([-+]) (\d\.\d+e[-+]\d+)f;",
                                                  fpart)]
-    dpart = src[src.index("__device__ inline double atan2_poly"):]
+    dpart = src[src.index("__device__ inline double atan2_pos"):]
     dpart = dpart[:dpart.index("double a = fma(t, p")]
     db = [float(x) for x in re.findall(r"double p = ([-+]?\d\.\d+e[-+]\d+);", dpart)]
     db += [float(x) for x in re.findall(r"p = fma\(p, u, ([-+]?[\d.]+(?:e[-+]\d+)?)\);", dpart)]

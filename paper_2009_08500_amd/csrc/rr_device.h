@@ -62,18 +62,20 @@ __host__ __device__ inline double rcp_nr(double x) {
 }
 
 // atan2 for double on the kernels' paths: r = min/max in [0, 1]; above
-// tan(pi/8) use atan r = pi/4 + atan((r - 1)/(r + 1)), so |t| <= tan(pi/8);
+// tan(pi/8) use atan r = pi/4 + atan((r - 1)/(r + 1)), so |t| <= tan(pi/8)
+// (with (min - max)/(min + max) for (r - 1)/(r + 1): one reciprocal either way);
 // atan t = t P(t^2) with P of degree 10 (a least-squares fit to atan(t)/t
 // at 64 Chebyshev nodes in t^2 on [0, tan^2(pi/8)], done in 40-digit
 // arithmetic and weighted for relative error, as fit_atan_poly.py beside
 // this file derives it: 3.5e-17 in exact arithmetic, ~1 ulp in double).
-template <class Ops = HwOps>
-__host__ __device__ inline double atan2_poly(double y, double x) {
-    const double ax = fabs(x), ay = fabs(y);
-    const double mx = fmax(ax, ay), mn = fmin(ax, ay);
-    const double r = mx > 0.0 ? mn * rcp_nr<Ops>(mx) : 0.0;
-    const bool big = r > 0.41421356237309503;             // tan(pi/8)
-    const double t = big ? (r - 1.0) * rcp_nr<Ops>(r + 1.0) : r;
+// atan2_pos: the same for y >= 0; with kNonZero (x, y) is not the origin.
+template <class Ops = HwOps, bool kNonZero = false>
+__host__ __device__ inline double atan2_pos(double y, double x) {
+    const double ax = fabs(x);
+    const double mx = fmax(ax, y), mn = fmin(ax, y);
+    const bool big = mn > 0.41421356237309503 * mx;      // tan(pi/8)
+    const double num = big ? mn - mx : mn, den = big ? mn + mx : mx;
+    const double t = kNonZero || mx > 0.0 ? num * rcp_nr<Ops>(den) : 0.0;
     const double u = t * t;
     double p = 2.11428279540593587e-02;
     p = fma(p, u, -4.34869344380681838e-02);
@@ -87,8 +89,12 @@ __host__ __device__ inline double atan2_poly(double y, double x) {
     p = fma(p, u, -3.33333333333284743e-01);
     p = fma(p, u, 1.0);
     double a = fma(t, p, big ? 0.78539816339744831 : 0.0);  // + pi/4
-    a = ay > ax ? 1.5707963267948966 - a : a;
-    a = x < 0.0 ? 3.1415926535897932 - a : a;
+    a = y > ax ? 1.5707963267948966 - a : a;
+    return x < 0.0 ? 3.1415926535897932 - a : a;
+}
+template <class Ops = HwOps>
+__host__ __device__ inline double atan2_poly(double y, double x) {
+    const double a = atan2_pos<Ops>(fabs(y), x);
     return y < 0.0 ? -a : a;
 }
 
