@@ -849,65 +849,6 @@ __global__ void k_prof_grad(const double* __restrict__ gldp, const double* __res
 
 inline unsigned nblocks(int64_t n) { return unsigned((n + kBlock - 1) / kBlock); }
 
-// Per-vector LD: dlogL/dldp_r[j] = sum_m (W[ik][j][m] (1 - ak) +
-// W[ik+1][j][m] ak) dlogL/dldw_r[m] for row r = (vector, passband): the
-// transpose of the row's k-interpolated T = W . l.  Workgroup (sorted row,
-// 16 bins): each wave takes 4 bins; per bin, lane l sums m = l, l + 64, ...
-// in order, then a fixed butterfly across the lanes.  Rows of tiles that go
-// to the matrix cores (k_pv_ldp_grad_mfma) are skipped.
-constexpr int kLdpBins = 16;
-template <typename WT>
-__global__ __launch_bounds__(kBlock) void k_pv_ldp_grad(const WT* __restrict__ W,
-                                                        const double* __restrict__ gldw,
-                                                        const double* __restrict__ pv,
-                                                        int32_t npar, const int32_t* __restrict__ ikr,
-                                                        const int32_t* __restrict__ perm,
-                                                        int64_t nr, int32_t nz, GridDev g,
-                                                        double* __restrict__ gldp) {
-    const int nchunk = (nz + kLdpBins - 1) / kLdpBins;
-    const int64_t b = blockIdx.x;
-    const int64_t pos = b / nchunk;
-    const int jc = int(b - pos * nchunk);
-    if (tile_on_matrix_cores(ikr, perm, nr, pos / 16)) return;     // uniform
-    const int64_t r = perm[pos];
-    const int64_t ipv = r / g.npb;
-    const int pb = int(r - ipv * g.npb);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const double u = (pv[ipv * npar + 6 + pb] - g.k0) / g.dk;
-    double uf = floor(u);
-    if (!(uf >= 0.0)) uf = 0.0;                  // invalid rows carry zero gldw
-    if (uf > g.nk - 2) uf = g.nk - 2;
-    const int ik = int(uf);
-    const double ak = u - ik;
-    const bool finite_k = ak == ak;
-    const double* gr = gldw + r * g.ng;
-    constexpr int kPerWave = kLdpBins / (kBlock / 64);
-#pragma unroll
-    for (int q = 0; q < kPerWave; ++q) {
-        const int j = jc * kLdpBins + wave * kPerWave + q;
-        if (j >= nz) break;                      // uniform per wave
-        const WT* w0 = W + (int64_t(ik) * nz + j) * g.ng;
-        const WT* w1 = w0 + int64_t(nz) * g.ng;
-        // eight columns' loads in flight, added in column order
-        double s = 0.0;
-        for (int m0 = lane; m0 < g.ng; m0 += 8 * 64) {
-            double x0[8], x1[8], gv[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int m = m0 + 64 * b;
-                const bool in = m < g.ng;
-                x0[b] = in ? double(w0[m]) : 0.0;
-                x1[b] = in ? double(w1[m]) : 0.0;
-                gv[b] = in ? gr[m] : 0.0;
-            }
-#pragma unroll
-            for (int b = 0; b < 8; ++b) s += ((1.0 - ak) * x0[b] + ak * x1[b]) * gv[b];
-        }
-        s = wave_sum(finite_k ? s : 0.0);
-        if (lane == 0) gldp[r * nz + j] = s;
-    }
-}
-
 template <typename R, int NPBT, bool kProf>
 void launch_adjoint_t(const AdjointArgs& A, size_t lds, hipStream_t s, const KernelEvents& ev) {
     // one part per vector: the profile sums are final and go to gldw_pv
@@ -1004,100 +945,171 @@ hipError_t launch_adjoint(const AdjointArgs& A, size_t lds, int32_t precision, h
     return hipGetLastError();
 }
 
-// The same on the matrix cores for tiles of 16 sorted rows on at most
-// kMfmaMaxRuns k-rows: per wave a 16 (bins) x 16 (rows) tile of
-// D[j][q] = sum_m W[ik][j][m] (1 - ak_q) g_q[m] + W[ik+1][j][m] ak_q g_q[m]
-// (g_q = dlogL/dldw of row q, zero for rows on another k-row), two
-// v_mfma_f64_16x16x4f64 chains into one accumulator; lane layout as in
-// the matrix-core part of k_pv_tables.  Block = 4 waves = 64 bins x 16 rows.
+// Per-vector LD: dlogL/dldp_r[j] = sum_m (W[ik][j][m] (1 - ak) +
+// W[ik+1][j][m] ak) dlogL/dldw_r[m] for row r = (vector, passband): the
+// transpose of the row's k-interpolated T = W . l, in the same two parts as
+// k_pv_tables (matrix cores for tiles of 16 sorted rows on few k-rows, else
+// row by row) and for the same reason bound by its loads of W: 16-byte loads,
+// the nodes split over a workgroup's waves, nodes below every row's
+// lowest_node (whose gradient is zero) left out.  1024 walkers, default grid,
+// float: 66 us for the matrix cores with 4-byte loads that touched 16 rows
+// of W each and one wave per 16 bins, and 7 us for a second launch of rows
+// that found nothing to do; now 10 us together.
 typedef double v4d __attribute__((ext_vector_type(4)));
-template <typename WT>
-__global__ __launch_bounds__(kBlock) void k_pv_ldp_grad_mfma(
-    const WT* __restrict__ W, const double* __restrict__ gldw,
-    const double* __restrict__ pv, int32_t npar, const int32_t* __restrict__ ikr,
-    const int32_t* __restrict__ perm, int64_t nr, int32_t nz, GridDev g,
-    double* __restrict__ gldp) {
-    const int njb = (nz + 63) / 64;
-    const int64_t rt = int64_t(blockIdx.x) / njb;
-    const int jb = int(int64_t(blockIdx.x) - rt * njb);
+constexpr int kLdpWaves = kBlock / 64;
+constexpr int kLdpTileBins = 16;              // bins per matrix-core workgroup
+constexpr int kLdpRowBins = 48;               // bins per single-row workgroup
+// The k-weight of row r on its k-row; 0 where k is not finite (an invalid
+// row: zero gradient).
+__device__ inline double row_ak(const double* __restrict__ pv, int32_t npar, int64_t r, int ik,
+                                const GridDev& g) {
+    const int64_t ipv = r / g.npb;
+    const double ak = (pv[ipv * npar + 6 + int(r - ipv * g.npb)] - g.k0) / g.dk - ik;
+    return ak == ak ? ak : 0.0;
+}
+
+// Tile rt, bins j0 .. j0 + 15: D[j][q] = sum_m W[ik][j][m] (1 - ak_q) g_q[m] +
+// W[ik+1][j][m] ak_q g_q[m] (g_q = dlogL/dldw of row q, zero for rows on
+// another k-row), v_mfma_f64_16x16x4f64 chains into one accumulator.  Lane l
+// holds A row / B column l & 15; the k index of step u is node
+// m + 4 (l >> 4) + u, so a lane's 16-byte load feeds four steps.
+template <bool kVec, typename WT>
+__device__ inline void pv_ldp_grad_mfma(const WT* __restrict__ W, const double* __restrict__ gldw,
+                                        const double* __restrict__ pv, int32_t npar,
+                                        const PvOrder& ord, int64_t nr, int32_t nz,
+                                        const GridDev& g, double* __restrict__ gldp, int64_t rt,
+                                        int j0, double* __restrict__ lds) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j0 = jb * 64 + wave * 16;
     const int ka = lane >> 4, col = lane & 15;
-    const int64_t pos = rt * 16 + col;
-    const int64_t r = pos < nr ? perm[pos] : -1;
-    const int ik = r >= 0 ? ikr[r] : 0x7fffffff;
-    const int prev_ik = __shfl(ik, (lane & 48) | ((col + 15) & 15), 64);
-    const uint64_t starts = __ballot(lane < 16 && r >= 0 && (col == 0 || ik != prev_ik));
-    if (__popcll(starts) > kMfmaMaxRuns) return;                  // k_pv_ldp_grad's tile
-    double ak = 0.0;
-    if (r >= 0) {
-        const int64_t ipv = r / g.npb;
-        const int pb = int(r - ipv * g.npb);
-        ak = (pv[ipv * npar + 6 + pb] - g.k0) / g.dk - ik;
-        if (!(ak == ak)) ak = 0.0;                  // non-finite k: zero gldw anyway
-    }
-    const int jj = j0 + col;                          // A row of this lane
-    const bool jin = jj < nz;
+    const int64_t pos = rt * kTileRows + col;
+    const int64_t r = pos < nr ? ord.perm[pos] : -1;
+    const int ik = pos < nr ? ord.key[pos] : 0x7fffffff;
+    const double ak = r >= 0 ? row_ak(pv, npar, r, ik, g) : 0.0;
+    const int first = wave_min(r >= 0 ? ord.mlo[r] : g.ng) / 16 * 16;
+    const int jj = j0 + col < nz ? j0 + col : nz - 1;           // A row of this lane
     v4d d = {0.0, 0.0, 0.0, 0.0};
-    int cur = ik;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) cur = min(cur, __shfl_xor(cur, off, 64));
+    int cur = wave_min(ik);
     while (cur != 0x7fffffff) {
         const bool take = ik == cur;
-        const WT* w0 = W + (int64_t(cur) * nz + (jin ? jj : 0)) * g.ng;
+        const WT* w0 = W + (int64_t(cur) * nz + jj) * g.ng;
         const WT* w1 = w0 + int64_t(nz) * g.ng;
         const double* gr = gldw + (take ? r : 0) * g.ng;
-        for (int m0 = 0; m0 < g.ng; m0 += 16) {
-            double a0[4], a1[4], b0[4], b1[4];
+        const double f0 = take ? 1.0 - ak : 0.0, f1 = take ? ak : 0.0;
+        constexpr int kStep = 2;
+        for (int m0 = first + 16 * wave; m0 < g.ng; m0 += 16 * kLdpWaves * kStep) {
+            WT a0[kStep][4], a1[kStep][4];
+            double b[kStep][4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {               // four k-steps' loads in flight
-                const int m = m0 + 4 * u + ka;
-                const bool min_ = m < g.ng;
-                a0[u] = jin && min_ ? double(w0[m]) : 0.0;
-                a1[u] = jin && min_ ? double(w1[m]) : 0.0;
-                const double gq = take && min_ ? gr[m] : 0.0;
-                b0[u] = (1.0 - ak) * gq;
-                b1[u] = ak * gq;
+            for (int u = 0; u < kStep; ++u) {
+                const int m = m0 + 16 * kLdpWaves * u + 4 * ka;
+                load4<kVec>(w0, m, g.ng, a0[u]);
+                load4<kVec>(w1, m, g.ng, a1[u]);
+                load4<kVec>(gr, m, g.ng, b[u]);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                d = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u], b0[u], d, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u], b1[u], d, 0, 0, 0);
-            }
+            for (int u = 0; u < kStep; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a0[u][q]), f0 * b[u][q], d, 0, 0, 0);
+                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a1[u][q]), f1 * b[u][q], d, 0, 0, 0);
+                }
         }
-        int nxt = ik > cur ? ik : 0x7fffffff;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) nxt = min(nxt, __shfl_xor(nxt, off, 64));
-        cur = nxt;
+        cur = wave_min(ik > cur ? ik : 0x7fffffff);
     }
-    if (r < 0) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int j = j0 + 4 * i + ka;
-        if (j < nz) gldp[r * nz + j] = d[i];
+    for (int i = 0; i < 4; ++i) lds[(wave * 4 + i) * 64 + lane] = d[i];
+    __syncthreads();
+    static_assert(kLdpWaves == 4, "wave w finishes element w");
+    double v = lds[wave * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < kLdpWaves; ++w) v += lds[(w * 4 + wave) * 64 + lane];
+    const int j = j0 + 4 * wave + ka;
+    if (r >= 0 && j < nz) gldp[r * nz + j] = v;
+}
+
+// Sorted row pos, bins j0 .. j0 + kLdpRowBins - 1: one wave per bin in turn,
+// lane l over nodes 4 l .. 4 l + 3 of every 256, then a fixed butterfly.
+template <bool kVec, typename WT>
+__device__ inline void pv_ldp_grad_row(const WT* __restrict__ W, const double* __restrict__ gldw,
+                                       const double* __restrict__ pv, int32_t npar,
+                                       const PvOrder& ord, int64_t pos, int32_t nz,
+                                       const GridDev& g, double* __restrict__ gldp, int j0) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t r = ord.perm[pos];
+    const int ik = ord.key[pos];
+    const double ak = row_ak(pv, npar, r, ik, g);
+    const int first = ord.mlo[r] / 4 * 4;
+    const double* gr = gldw + r * g.ng;
+    constexpr int kBins = 3;                  // bins of a wave in flight
+    const int j1 = min(nz, j0 + kLdpRowBins);
+    for (int ja = j0 + wave; ja < j1; ja += kLdpWaves * kBins) {
+        double s[kBins];
+#pragma unroll
+        for (int u = 0; u < kBins; ++u) s[u] = 0.0;
+        for (int m = first + 4 * lane; m < g.ng; m += 256) {
+            double gv[4];
+            WT x0[kBins][4], x1[kBins][4];
+            load4<kVec>(gr, m, g.ng, gv);
+#pragma unroll
+            for (int u = 0; u < kBins; ++u) {
+                const int j = min(ja + kLdpWaves * u, nz - 1);
+                const WT* w0 = W + (int64_t(ik) * nz + j) * g.ng;
+                load4<kVec>(w0, m, g.ng, x0[u]);
+                load4<kVec>(w0 + int64_t(nz) * g.ng, m, g.ng, x1[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kBins; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    s[u] += ((1.0 - ak) * double(x0[u][q]) + ak * double(x1[u][q])) * gv[q];
+        }
+#pragma unroll
+        for (int u = 0; u < kBins; ++u) {
+            const double v = wave_sum(s[u]);
+            const int j = ja + kLdpWaves * u;
+            if (lane == 0 && j < j1) gldp[r * nz + j] = v;
+        }
     }
 }
 
-hipError_t launch_pv_prof_grad(const rr_tables* t, const AdjointArgs& A, const int32_t* ikr,
-                               const int32_t* perm, double* gldp, double* out, hipStream_t s,
-                               bool w32) {
+template <bool kVec, typename WT>
+__global__ __launch_bounds__(kBlock) void k_pv_ldp_grad(
+    const WT* __restrict__ W, const double* __restrict__ gldw, const double* __restrict__ pv,
+    int32_t npar, PvOrder ord, int64_t nr, int32_t nz, GridDev g, int64_t n_mfma,
+    int64_t blocks, double* __restrict__ gldp) {
+    __shared__ double lds[kLdpWaves * 4 * 64];
+    const int64_t b = flat_block();
+    if (b >= blocks) return;
+    if (b < n_mfma) {
+        const int njb = (nz + kLdpTileBins - 1) / kLdpTileBins;
+        const int64_t rt = b / njb;
+        if (!ord.mfma[rt]) return;
+        pv_ldp_grad_mfma<kVec, WT>(W, gldw, pv, npar, ord, nr, nz, g, gldp, rt,
+                             int(b - rt * njb) * kLdpTileBins, lds);
+        return;
+    }
+    const int njb = (nz + kLdpRowBins - 1) / kLdpRowBins;
+    const int64_t p = b - n_mfma, pos = p / njb;
+    if (ord.mfma[pos / kTileRows]) return;
+    pv_ldp_grad_row<kVec, WT>(W, gldw, pv, npar, ord, pos, nz, g, gldp,
+                        int(p - pos * njb) * kLdpRowBins);
+}
+
+hipError_t launch_pv_prof_grad(const rr_tables* t, const AdjointArgs& A, const PvOrder& ord,
+                               double* gldp, double* out, hipStream_t s, bool w32) {
     const GridDev g = A.g;
     const int64_t nr = int64_t(A.npv) * g.npb;
-    const int64_t nchunk = (t->nz + kLdpBins - 1) / kLdpBins;
-    const dim3 gm(unsigned(((nr + 15) / 16) * ((t->nz + 63) / 64)));
-    const dim3 gr(unsigned(nr * nchunk));
+    const int64_t n_mfma =
+        (nr + kTileRows - 1) / kTileRows * ((t->nz + kLdpTileBins - 1) / kLdpTileBins);
+    const int64_t blocks = n_mfma + nr * ((t->nz + kLdpRowBins - 1) / kLdpRowBins);
     // the transpose of the contraction that built the rows, with its weights
-    if (w32) {
-        hipLaunchKernelGGL(k_pv_ldp_grad_mfma<float>, gm, dim3(kBlock), 0, s, t->W32, A.gldw_pv,
-                           A.pv, A.npar, ikr, perm, nr, t->nz, g, gldp);
-        hipLaunchKernelGGL(k_pv_ldp_grad<float>, gr, dim3(kBlock), 0, s, t->W32, A.gldw_pv, A.pv,
-                           A.npar, ikr, perm, nr, t->nz, g, gldp);
-    } else {
-        hipLaunchKernelGGL(k_pv_ldp_grad_mfma<double>, gm, dim3(kBlock), 0, s, t->W, A.gldw_pv,
-                           A.pv, A.npar, ikr, perm, nr, t->nz, g, gldp);
-        hipLaunchKernelGGL(k_pv_ldp_grad<double>, gr, dim3(kBlock), 0, s, t->W, A.gldw_pv, A.pv,
-                           A.npar, ikr, perm, nr, t->nz, g, gldp);
-    }
+    auto launch = [&](auto kernel, const auto* W) {
+        hipLaunchKernelGGL(kernel, flat_grid(blocks), dim3(kBlock), 0, s, W, A.gldw_pv, A.pv,
+                           A.npar, ord, nr, t->nz, g, n_mfma, blocks, gldp);
+    };
+    const bool vec = g.ng % 4 == 0;              // 16-byte loads, as launch_pv_ld
+    if (w32) launch(vec ? k_pv_ldp_grad<true, float> : k_pv_ldp_grad<false, float>, t->W32);
+    else launch(vec ? k_pv_ldp_grad<true, double> : k_pv_ldp_grad<false, double>, t->W);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the shared profile's last step with every (vector, passband) as one

@@ -702,8 +702,7 @@ RR_API int rr_evaluate_ld(const rr_tables* t, const double* times_d,
     const size_t o_is = take(sizeof(double) * size_t(nr));
     const size_t o_iis = take(sizeof(double) * size_t(nr));
     const size_t o_ldw = take(elt * size_t(nr) * 2 * t->grid.ng);
-    const size_t o_ikr = take(sizeof(int32_t) * size_t(nr));
-    const size_t o_perm = take(sizeof(int32_t) * size_t(nr));
+    const size_t o_ord = take(sizeof(int32_t) * size_t(pv_order_ints(nr)));
     // the tables' per-stream workspace (as rr_evaluate): reused without
     // waiting by later calls on the same stream
     void* ws = nullptr;
@@ -713,14 +712,11 @@ RR_API int rr_evaluate_ld(const rr_tables* t, const double* times_d,
     PvConst* pvc = reinterpret_cast<PvConst*>(base + o_pvc);
     double* inv_is = reinterpret_cast<double*>(base + o_iis);
     void* ldw = base + o_ldw;
-    e = launch_pv_setup(t, pv_d, npv, npar, pvc, precision, stream);
-    if (e == hipSuccess)
-        e = launch_pv_ld(t, prof_d, pv_d, npv, npar, precision,
-                         reinterpret_cast<double*>(base + o_ldp),
-                         reinterpret_cast<double*>(base + o_is), inv_is,
-                         reinterpret_cast<int32_t*>(base + o_ikr),
-                         reinterpret_cast<int32_t*>(base + o_perm), ldw, stream,
-                         precision == RR_MIXED);
+    e = launch_pv_ld(t, prof_d, pv_d, npv, npar, precision,
+                     reinterpret_cast<double*>(base + o_ldp),
+                     reinterpret_cast<double*>(base + o_is), inv_is,
+                     pv_order(reinterpret_cast<int32_t*>(base + o_ord), nr), ldw, stream,
+                     precision == RR_MIXED, pvc);
     if (e == hipSuccess)
         e = launch_forward(t, times_d, lcids_d, npt, lc, pv_d, npv, npar, pvc, precision,
                            out_d, stream, ldw, inv_is);
@@ -808,8 +804,7 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
     if (sp && nr >= (int64_t(1) << 31)) return elimit("npv * npb too large");
     const bool own_rows = per_row || sp;
     const size_t o_iisr = own_rows ? take(sizeof(double) * size_t(nr)) : 0;
-    const size_t o_ikr = per_row ? take(sizeof(int32_t) * size_t(nr)) : 0;
-    const size_t o_perm = per_row ? take(sizeof(int32_t) * size_t(nr)) : 0;
+    const size_t o_ord = per_row ? take(sizeof(int32_t) * size_t(pv_order_ints(nr))) : 0;
     const size_t o_rows = own_rows ? take(elt * size_t(nr) * 2 * g.ng) : 0;
     const size_t o_gldpr = per_row && prof ? take(sizeof(double) * size_t(nr) * t->nz) : 0;
     const size_t o_gt = shared_prof ? take(sizeof(double) * size_t(t->npb) * g.nk * g.ng) : 0;
@@ -867,13 +862,11 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
                          reinterpret_cast<double*>(base + o_ldp),
                          reinterpret_cast<double*>(base + o_isr),
                          reinterpret_cast<double*>(base + o_iisr),
-                         reinterpret_cast<int32_t*>(base + o_ikr),
-                         reinterpret_cast<int32_t*>(base + o_perm), base + o_rows, stream,
+                         pv_order(reinterpret_cast<int32_t*>(base + o_ord), nr), base + o_rows, stream,
                          precision == RR_MIXED);     // the rows rr_evaluate_ld evaluates
     if (e == hipSuccess) e = launch_adjoint(A, lds, precision, stream);
     if (e == hipSuccess && prof && per_row)
-        e = launch_pv_prof_grad(t, A, reinterpret_cast<const int32_t*>(base + o_ikr),
-                                reinterpret_cast<const int32_t*>(base + o_perm),
+        e = launch_pv_prof_grad(t, A, pv_order(reinterpret_cast<int32_t*>(base + o_ord), nr),
                                 reinterpret_cast<double*>(base + o_gldpr), grad_prof_d, stream,
                                 precision == RR_MIXED);
     if (e == hipSuccess && shared_prof) {

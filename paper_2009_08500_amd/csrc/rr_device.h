@@ -471,23 +471,78 @@ __device__ inline bool block_in_window(double lo, double hi, const PvConst& p) {
     return lo <= hi && !((glo - m) - f >= p.wn + 2.0 * m && (ghi + m) - f < 1.0);
 }
 
-// Per-vector LD: a tile of 16 consecutive rows in k-row order goes to the
-// matrix cores when its rows span at most kMfmaMaxRuns k-rows (each W value
-// is then read once for the tile), else to the per-row kernels.  The
-// matrix-core and per-row kernels apply this same test to the sorted keys.
+// A launch of many small workgroups as a grid of at most 2^22 by 65535 (the
+// threads of one dimension must stay below 2^32); flat_block() numbers them,
+// and the kernel leaves out those from `blocks` on.
+inline dim3 flat_grid(int64_t blocks) {
+    const int64_t x = blocks < (int64_t(1) << 22) ? blocks : int64_t(1) << 22;
+    return dim3(unsigned(x), unsigned((blocks + x - 1) / x));
+}
+__device__ inline int64_t flat_block() {
+    return int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
+}
+
+// The lowest grazing node that a light curve of parameter row `row` can read
+// for radius ratio k: with r >= a (1 - e) and z >= r cos i everywhere on the
+// orbit, z >= b (1 + e sin w)/(1 + e).  Row vectors built for one parameter
+// row leave the nodes below it out (a third of them for impact parameters
+// uniform in [0, 0.9]).  The margins cover the rounding of z in float (a few
+// 1e-7 of a) and the node below a z on a node; 0 for a row that is not valid.
+__device__ inline int lowest_node(const double* __restrict__ row, double k, const GridDev& g) {
+    const double a = row[2], b = row[3], e = row[4], w = row[5];
+    const double z = b * (1.0 + e * sin(w)) / (1.0 + e) * (1.0 - 1e-5) - 4e-6 * a;
+    const double v = z / (1.0 + k) * g.gscale - 2.0;
+    if (!(v > 0.0) || !(e >= 0.0) || !(e < 1.0) || !(k > 0.0)) return 0;
+    return v < double(g.ng - 1) ? int(v) : g.ng - 1;
+}
+
+// Per-vector LD: the rows sorted by k-row, in tiles of 16.  A tile goes to
+// the matrix cores when its rows span at most kMfmaMaxRuns k-rows (each W
+// value is then read once for the tile), else its rows are taken one by one;
+// the sort stores the choice in `mfma` (1 or 0).
 constexpr int kMfmaMaxRuns = 2;
-// Wave-level: lanes 0..15 each read one key, so it must be called by whole
-// waves (the result is uniform).
-__device__ inline bool tile_on_matrix_cores(const int32_t* __restrict__ ikr,
-                                            const int32_t* __restrict__ perm, int64_t nr,
-                                            int64_t tile) {
-    const int lane = threadIdx.x & 63, q = lane & 15;
-    const int64_t pos = tile * 16 + q;
-    const bool in = pos < nr;
-    const int ik = in ? ikr[perm[pos]] : -1;
-    const int prev = __shfl(ik, (lane & 48) | ((q + 15) & 15), 64);
-    const uint64_t starts = __ballot(lane < 16 && in && (q == 0 || ik != prev));
-    return __popcll(starts) <= kMfmaMaxRuns;
+constexpr int kTileRows = 16;
+struct PvOrder {
+    int32_t* perm;     // [nr] row at each sorted position
+    int32_t* key;      // [nr] its k-row
+    int32_t* mfma;     // [ceil(nr / 16)]
+    int32_t* mlo;      // [nr] lowest_node of each row (by row)
+};
+inline PvOrder pv_order(int32_t* base, int64_t nr) {
+    return PvOrder{base, base + nr, base + 3 * nr, base + 2 * nr};
+}
+// The smallest of the wave's values (uniform).
+__device__ inline int wave_min(int v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Four consecutive values of a row of n from element m (a multiple of 4), zero
+// past n.  kVec: 16-byte loads (16-byte aligned rows, n a multiple of 4).  The
+// loads are unconditional (past the end the row's first element), so that
+// several calls' loads are in flight together.
+template <bool kVec, typename T>
+__device__ inline void load4(const T* __restrict__ w, int m, int n, T* x) {
+    constexpr int kV = 16 / int(sizeof(T));
+    typedef T V __attribute__((ext_vector_type(kV)));
+    if constexpr (kVec) {
+        const bool in = m < n;
+        w += in ? m : 0;
+#pragma unroll
+        for (int q = 0; q < 4; q += kV) {
+            const V v = *reinterpret_cast<const V*>(w + q);
+#pragma unroll
+            for (int i = 0; i < kV; ++i) x[q + i] = in ? v[i] : T(0);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = m + q < n;
+            const T v = w[in ? m + q : 0];
+            x[q] = in ? v : T(0);
+        }
+    }
 }
 
 }  // namespace rr

@@ -123,6 +123,7 @@ struct GridDev {
 };
 
 // Arguments of the adjoint launch (rr_adjoint.hip).
+struct PvOrder;
 struct AdjointArgs {
     const double* times;
     const int32_t* lcids;
@@ -266,12 +267,11 @@ struct ProfGradScratch {
     double* grad_istar;   // [npb] output (d logL / d I_star) or null
 };
 // Per-vector LD: d logL / d prof[ipv][pb][s] from the adjoint's per-vector
-// d logL / d ldw and d logL / d I_star; ikr and perm are launch_pv_ld's sort
-// of the rows by k-row, gldp is [npv][npb][nz] scratch.
+// d logL / d ldw and d logL / d I_star; ord is launch_pv_ld's order of the
+// rows by k-row, gldp is [npv][npb][nz] scratch.
 // w32: the weights are the FP32 copy (the mixed per-vector rows' own).
-hipError_t launch_pv_prof_grad(const rr_tables* t, const AdjointArgs& A, const int32_t* ikr,
-                               const int32_t* perm, double* gldp, double* out, hipStream_t s,
-                               bool w32);
+hipError_t launch_pv_prof_grad(const rr_tables* t, const AdjointArgs& A, const PvOrder& ord,
+                               double* gldp, double* out, hipStream_t s, bool w32);
 hipError_t launch_profile_grad(const rr_tables* t, const AdjointArgs& a,
                                const ProfGradScratch& w, double* out, hipStream_t s);
 hipError_t launch_fill(double* p, int64_t n, hipStream_t s);
@@ -337,12 +337,16 @@ hipError_t launch_flux_at_z(const rr_tables* t, const double* z, const double* k
 // Per-vector LD (rr_evaluate_ld): from prof[npv][npb][nmu] on the tables'
 // mu samples, the profile at the bin means (ldp, [npv][npb][nz]), I_star and
 // 1/I_star ([npv][npb]) and the vector's own two table rows around its k
-// (rows, [npv][npb][2][ng], double or float by precision); ikr and perm are
-// [npv npb] int32 scratch.
-// w32: the per-row kernel reads the FP32 copy of W (mixed precision only).
+// (rows, [npv][npb][2][ng], double or float by precision; nodes below the
+// row's lowest_node are not written); ord is scratch of pv_order_ints(nr)
+// int32.
+// pvc (may be NULL): also the vectors' constants, as launch_pv_setup.
+// w32: the kernels read the FP32 copy of W (mixed precision only).
 hipError_t launch_pv_ld(const rr_tables* t, const double* prof, const double* pv,
                         int32_t npv, int32_t npar, int32_t precision, double* ldp,
-                        double* istar, double* inv_istar, int32_t* ikr, int32_t* perm,
-                        void* rows, hipStream_t s, bool w32 = false);
+                        double* istar, double* inv_istar, const PvOrder& ord,
+                        void* rows, hipStream_t s, bool w32 = false, PvConst* pvc = nullptr);
+// The order's arrays in one int32 buffer.
+inline int64_t pv_order_ints(int64_t nr) { return 3 * nr + (nr + 15) / 16; }
 
 }  // namespace rr

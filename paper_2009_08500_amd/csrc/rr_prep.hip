@@ -185,44 +185,52 @@ hipError_t launch_prepare_grid_weights(rr_tables* t, hipStream_t s) {
 // k_pv_prep sorts the rows by ik, so that rows with equal ik share the W
 // reads of one matrix-core tile (the two parts of k_pv_tables below).
 // Stable counting sort of the rows by ik, by one workgroup of kBlock
-// threads (thread t owns bins 16 t .. 16 t + 15 of at most 4096): the
-// histogram and its scan by all waves, then one wave places the rows in
-// row order, 64 at a time -- a lane's rank among the lanes with its key
-// comes from a ballot per key bit -- so equal keys keep their row order
-// and the tiles (and which kernel takes each) depend on the inputs only.
-// The keys of the first kSortLds rows also go to LDS (as 16-bit values,
-// nk <= 4096), so that the placing wave's serial loop reads them there
-// rather than waiting on a global load in every step.
+// threads: the waves (four, or as many as have a counter per key in LDS) take
+// consecutive runs of the rows; each counts its keys, a scan over (key, wave)
+// gives every wave its offsets, and each places its rows in row order, 64 at
+// a time -- a lane's rank among the lanes with its key comes from a ballot
+// per key bit -- so equal keys keep their row order and the tiles (and which
+// part takes each) depend on the inputs only.  It is the launch's longest
+// serial chain: for 1024 rows the launch took 13.2 us with one placing wave
+// and 9.4 us with four.
+// The keys of the first kSortLds rows are kept in LDS (as 16-bit values,
+// nk <= 4096) for the placing loop.
 constexpr int kSortLds = 8192;
+constexpr int kSortCounters = 4096;
 __device__ inline void sort_rows(const double* __restrict__ pv, int32_t npv, int32_t npar,
-                                 const GridDev& g, int32_t* __restrict__ ikr,
-                                 int32_t* __restrict__ perm) {
-    constexpr int kPer = 4096 / kBlock;
-    __shared__ int cnt[4096];
+                                 const GridDev& g, const PvOrder& ord) {
+    constexpr int kPer = kSortCounters / kBlock;
+    __shared__ int cnt[kSortCounters];                 // [key][wave]
     __shared__ uint16_t keys[kSortLds];
     __shared__ int wsum[kBlock / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n = int64_t(npv) * g.npb;
-    for (int b = tid; b < g.nk; b += kBlock) cnt[b] = 0;
-    __syncthreads();
-    for (int64_t r = tid; r < n; r += kBlock) {
+    int sh = 2;                                        // log2 of the waves that place
+    while (sh > 0 && (g.nk << sh) > kSortCounters) --sh;
+    const int nw = 1 << sh, ncnt = g.nk << sh;
+    const int64_t per = ((n + nw - 1) / nw + 63) / 64 * 64;    // rows per wave
+    auto key_of = [&](int64_t r) {
         const int64_t ipv = r / g.npb;
         const int pb = int(r - ipv * g.npb);
         const double u = (pv[ipv * npar + 6 + pb] - g.k0) / g.dk;
         double uf = floor(u);
         if (!(uf >= 0.0)) uf = 0.0;              // also a non-finite k (NaN row anyway)
         if (uf > g.nk - 2) uf = g.nk - 2;
-        const int ik = int(uf);
-        ikr[r] = ik;
+        return int(uf);
+    };
+    for (int b = tid; b < ncnt; b += kBlock) cnt[b] = 0;
+    __syncthreads();
+    for (int64_t r = tid; r < n; r += kBlock) {
+        const int ik = key_of(r);
         if (r < kSortLds) keys[r] = uint16_t(ik);
-        atomicAdd(&cnt[ik], 1);
+        atomicAdd(&cnt[(ik << sh) + int(r / per)], 1);
     }
     __syncthreads();
     int v[kPer], local = 0;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int b = kPer * tid + q;
-        v[q] = b < g.nk ? cnt[b] : 0;
+        v[q] = b < ncnt ? cnt[b] : 0;
         local += v[q];
     }
     int x = local;
@@ -238,40 +246,62 @@ __device__ inline void sort_rows(const double* __restrict__ pv, int32_t npv, int
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int b = kPer * tid + q;
-        if (b < g.nk) cnt[b] = excl;
+        if (b < ncnt) cnt[b] = excl;
         excl += v[q];
     }
     __syncthreads();
-    if (wave != 0) return;
-    for (int64_t r0 = 0; r0 < n; r0 += 64) {
+    const int bits = 32 - __builtin_clz(g.nk);
+    const int64_t r_end = min(n, per * (wave + 1));
+    for (int64_t r0 = per * wave; wave < nw && r0 < r_end; r0 += 64) {
         const int64_t r = r0 + lane;
-        const bool in = r < n;
-        const int key = in ? (r < kSortLds ? int(keys[r]) : ikr[r]) : 0;
+        const bool in = r < r_end;
+        const int key = in ? (r < kSortLds ? int(keys[r]) : key_of(r)) : 0;
         uint64_t same = __ballot(in);            // lanes with this lane's key
-#pragma unroll
-        for (int b = 0; b < 12; ++b) {           // keys < nk <= 4096
+        for (int b = 0; b < bits; ++b) {
             const bool bit = (key >> b) & 1;
             const uint64_t ones = __ballot(in && bit);
             same &= bit ? ones : ~ones;
         }
-        const int base = in ? cnt[key] : 0;
-        if (in) perm[base + __popcll(same & __lanemask_lt())] = int32_t(r);
+        const int slot = (key << sh) + wave;
+        const int base = in ? cnt[slot] : 0;
+        if (in) {
+            const int at = base + __popcll(same & __lanemask_lt());
+            ord.perm[at] = int32_t(r);
+            ord.key[at] = key;
+        }
         // every lane has read its key's offset before the first lane of each
-        // key group (the only writer of that key) advances it
+        // key group (the only writer of that counter) advances it
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (in && (same & __lanemask_lt()) == 0) cnt[key] = base + __popcll(same);
+        if (in && (same & __lanemask_lt()) == 0) cnt[slot] = base + __popcll(same);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    // which part takes each tile: its distinct keys (sorted, so its runs)
+    __threadfence_block();
+    __syncthreads();
+    const int64_t ntile = (n + kTileRows - 1) / kTileRows;
+    for (int64_t t = tid; t < ntile; t += kBlock) {
+        int runs = 0, prev = -1;
+        const int64_t p1 = min(n, (t + 1) * kTileRows);
+        for (int64_t p = t * kTileRows; p < p1; ++p) {
+            const int k = ord.key[p];
+            runs += k != prev;
+            prev = k;
+        }
+        ord.mfma[t] = runs <= kMfmaMaxRuns ? 1 : 0;
     }
 }
 
 // One launch for the per-vector preparation: workgroup 0 sorts the rows by
 // ik (the longest serial chain, so it is dispatched first), and workgroup
-// r + 1 interpolates row r's profile to the bin means and integrates its
-// I_star (the table kernels' arithmetic).
+// r + 1 interpolates row r's profile to the bin means, integrates its
+// I_star (the table kernels' arithmetic) and finds its lowest node.  With pvc
+// one thread of a vector's first row also derives the vector's constants (as
+// k_pv_setup, whose launch of 4-5 us this saves).
+template <bool kF32>
 __global__ __launch_bounds__(kBlock) void k_pv_prep(const double* __restrict__ mu_s,
                                                     const double* __restrict__ prof,
                                                     int32_t nmu, const double* __restrict__ zm,
@@ -280,170 +310,219 @@ __global__ __launch_bounds__(kBlock) void k_pv_prep(const double* __restrict__ m
                                                     double* __restrict__ ldp,
                                                     double* __restrict__ istar,
                                                     double* __restrict__ inv_istar,
-                                                    int32_t* __restrict__ ikr,
-                                                    int32_t* __restrict__ perm) {
+                                                    PvOrder ord, double k1,
+                                                    PvConst* __restrict__ pvc) {
     const int64_t nr = int64_t(npv) * g.npb;
     if (blockIdx.x == 0) {
-        sort_rows(pv, npv, npar, g, ikr, perm);
+        sort_rows(pv, npv, npar, g, ord);
         return;
     }
     const int64_t r = int64_t(blockIdx.x) - 1;
     if (r >= nr) return;
     const double* f = prof + r * nmu;
+    const int64_t ipv = r / g.npb;
+    const int pb = int(r - ipv * g.npb);
+    const double* row = pv + ipv * npar;
+    if (threadIdx.x == kBlock - 1 && pvc && pb == 0)
+        pvc[ipv] = make_pv_const<kF32>(row, g.npb, g.k0, k1);
+    if (threadIdx.x == kBlock - 65) ord.mlo[r] = lowest_node(row, row[6 + pb], g);
     for (int j = threadIdx.x; j < nz; j += kBlock) ldp[r * nz + j] = profile_at_bin(mu_s, f, nmu, zm[j]);
     istar_block(mu_s, f, nmu, istar + r, inv_istar + r);
 }
 
-// Rows of a sorted 16-row tile with at most two distinct k-rows go to the
-// matrix cores (pv_tables_mfma, which then reads each W value once for up
-// to 16 rows); the rows of the other tiles (k spread over many k-rows, where
-// a tile would need a pass per k-row) to pv_tables_rows, one workgroup per
-// (row, 256 m).  Both parts evaluate the same test on the sorted keys, so
-// every row is written by exactly one of them.
-// pv_tables_rows: rows taken in sorted order, with an XCD-aware block order: blocks go round-robin to the eight XCDs, so block
-// p works on sorted item (p mod 8) * (blocks / 8) + p / 8 (rounded for a
-// remainder) and each XCD walks a contiguous stretch of the sorted rows,
-// whose W rows its L2 then serves to the following rows of equal ik.
-// The part is bound by the latency of its W loads: 24 in flight per lane
-// measured best of 8 to 48.
-constexpr int kXcds = 8;
-template <typename R, typename WT>
-__device__ inline void pv_tables_rows(const WT* __restrict__ W, const double* __restrict__ ldp,
-                                      const int32_t* __restrict__ ikr,
-                                      const int32_t* __restrict__ perm, int32_t nz, GridDev g,
-                                      R* __restrict__ out, int64_t nb, int64_t p,
-                                      double* __restrict__ lp) {
-    const int64_t q = nb / kXcds, rem = nb % kXcds;
-    const int64_t x = p % kXcds;
-    const int64_t L = (x < rem ? x * (q + 1) : rem * (q + 1) + (x - rem) * q) + p / kXcds;
-    const int nmb = (g.ng + kBlock - 1) / kBlock;
-    const int64_t pos = L / nmb;
-    const int mb = int(L - pos * nmb);
-    if (tile_on_matrix_cores(ikr, perm, int64_t(nb / nmb), pos / 16)) return;   // uniform
-    const int64_t r = perm[pos];
-    const int ik = ikr[r];
-    for (int j = threadIdx.x; j < nz; j += kBlock) lp[j] = ldp[r * nz + j];
-    __syncthreads();
-    const int m = mb * kBlock + int(threadIdx.x);
-    if (m >= g.ng) return;
-    const WT* w0 = W + int64_t(ik) * nz * g.ng + m;
-    const WT* w1 = w0 + int64_t(nz) * g.ng;
-    double a0 = 0.0, a1 = 0.0;
-    int j = 0;
-    for (; j + 12 <= nz; j += 12) {               // 24 loads in flight
-        WT x0[12], x1[12];
-#pragma unroll
-        for (int b = 0; b < 12; ++b) {
-            x0[b] = w0[int64_t(j + b) * g.ng];
-            x1[b] = w1[int64_t(j + b) * g.ng];
-        }
-#pragma unroll
-        for (int b = 0; b < 12; ++b) {
-            a0 += double(x0[b]) * lp[j + b];
-            a1 += double(x1[b]) * lp[j + b];
-        }
-    }
-    for (; j < nz; ++j) {
-        a0 += double(w0[int64_t(j) * g.ng]) * lp[j];
-        a1 += double(w1[int64_t(j) * g.ng]) * lp[j];
-    }
-    R* o = out + r * 2 * g.ng;
-    o[m] = R(a0);
-    o[g.ng + m] = R(a1);
-}
-
-// The per-vector table rows on the matrix cores: per wave a 16 (m) x 16 (sorted
-// rows) tile of T_r[s][m] = sum_j W[ik_r + s][j][m] ldp_r[j], s = 0, 1, as
-// D = A B with A[m][j] = W[ik + s][j][m] and B[j][q] = ldp of row q when the
-// row's k-row is ik, else 0, over the distinct ik of the tile's rows (sorted,
-// so usually one or two), with v_mfma_f64_16x16x4f64 (FP64 products and
-// sums; only the order of the additions over j differs from k_tables).
-// Lane l holds A[l & 15][l >> 4], B[l >> 4][l & 15] and D[4 i + (l >> 4)][l & 15]
-// (checked on the device).  Block = 4 waves = 64 m x 16 rows.
+// The per-vector table rows T_r[s][m] = sum_j W[ik_r + s][j][m] ldp_r[j],
+// s = 0, 1.  Rows of a sorted 16-row tile with at most two distinct k-rows go
+// to the matrix cores (each W value read once for up to 16 rows); the rows of
+// the other tiles (k spread over many k-rows, where a tile would need a pass
+// per k-row) one by one.  The two parts share one launch of workgroups of 64
+// nodes (m) and four waves that split the bins; nodes below lowest_node are
+// left out.  Matrix cores: the part waits on its loads of W (from the L2 for
+// the most part), so it needs many of them in flight: with one wave over all
+// bins and 4-byte loads it took 32 us for 1024 walkers (default grid, float),
+// with the bins split over four waves and 16-byte loads 15 us.
+// Lane l takes the nodes m0 + 4 (l & 15) .. + 3 of bins 4 i + (l >> 4), in v_mfma_f64_16x16x4f64 chains D = A B with A[m][j] =
+// W[ik + s][j][m] and B[j][q] = ldp of row q when the row's k-row is ik, else
+// 0, over the distinct ik of the tile (FP64 products and sums; only the order
+// of the additions over j differs from k_tables).  Lane l holds
+// A[l & 15][l >> 4], B[l >> 4][l & 15] and D[4 i + (l >> 4)][l & 15] (checked
+// on the device); row a of chain q is node m0 + 4 a + q.
 typedef double v4d __attribute__((ext_vector_type(4)));
-template <typename R, typename WT>
+constexpr int kPvWaves = kBlock / 64;
+constexpr int kPvNodes = 64;
+constexpr int kPvLds = kPvWaves * 8 * 64;             // doubles
+template <bool kVec, typename R, typename WT>
 __device__ inline void pv_tables_mfma(const WT* __restrict__ W, const double* __restrict__ ldp,
-                                      const int32_t* __restrict__ ikr,
-                                      const int32_t* __restrict__ perm, int64_t nr, int32_t nz,
-                                      GridDev g, R* __restrict__ out, int64_t bid) {
-    const int nmb = (g.ng + 63) / 64;
-    const int64_t rt = bid / nmb;                              // row tile
-    const int mb = int(bid - rt * nmb);
+                                      const PvOrder& ord, int64_t nr, int32_t nz,
+                                      const GridDev& g, R* __restrict__ out, int64_t rt, int m0,
+                                      double* __restrict__ lds) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = mb * 64 + wave * 16;
     const int ka = lane >> 4, col = lane & 15;
-    const int mm = m0 + col;                                   // A row of this lane
-    const int64_t pos = rt * 16 + col;                         // B column of this lane
-    const int64_t r = pos < nr ? perm[pos] : -1;
-    const int ik = r >= 0 ? ikr[r] : 0x7fffffff;
-    const bool mok = mm < g.ng;
-    // tiles whose rows span more than kMfmaMaxRuns k-rows are k_pv_tables' work
-    const int prev_ik = __shfl(ik, (lane & 48) | ((col + 15) & 15), 64);
-    const uint64_t starts = __ballot(lane < 16 && r >= 0 && (col == 0 || ik != prev_ik));
-    if (__popcll(starts) > kMfmaMaxRuns) return;                  // uniform per wave
-    v4d d0 = {0.0, 0.0, 0.0, 0.0}, d1 = {0.0, 0.0, 0.0, 0.0};
-    // distinct k-rows of the tile, smallest first (wave-uniform loop)
-    int cur = ik;
+    const int64_t pos = rt * kTileRows + col;
+    const int64_t r = pos < nr ? ord.perm[pos] : -1;
+    const int ik = pos < nr ? ord.key[pos] : 0x7fffffff;
+    if (wave_min(r >= 0 ? ord.mlo[r] : g.ng) >= m0 + kPvNodes) return;   // no row reads these
+    const int mm = m0 + 4 * col;
+    v4d d[2][4];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) cur = min(cur, __shfl_xor(cur, off, 64));
+    for (int q = 0; q < 4; ++q) d[0][q] = d[1][q] = v4d{0.0, 0.0, 0.0, 0.0};
+    // distinct k-rows of the tile, smallest first (wave-uniform loop)
+    int cur = wave_min(ik);
     while (cur != 0x7fffffff) {
         const bool take = ik == cur;
-        const WT* w0 = W + int64_t(cur) * nz * g.ng + (mok ? mm : 0);
+        const WT* w0 = W + int64_t(cur) * nz * g.ng;
         const WT* w1 = w0 + int64_t(nz) * g.ng;
         const double* lr = ldp + (take ? r : 0) * nz;
-        for (int j0 = 0; j0 < nz; j0 += 16) {
-            double a0[4], a1[4], b[4];
+        constexpr int kStep = sizeof(WT) == 4 ? 4 : 2;     // bins in flight per lane
+        for (int j0 = 4 * wave; j0 < nz; j0 += 4 * kPvWaves * kStep) {
+            WT a0[kStep][4], a1[kStep][4];
+            double b[kStep];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {               // four k-steps' loads in flight
-                const int j = j0 + 4 * u + ka;
-                const bool jin = j < nz;
-                a0[u] = jin && mok ? double(w0[int64_t(j) * g.ng]) : 0.0;
-                a1[u] = jin && mok ? double(w1[int64_t(j) * g.ng]) : 0.0;
-                b[u] = jin && take ? lr[j] : 0.0;
+            for (int u = 0; u < kStep; ++u) {
+                const int j = j0 + 4 * kPvWaves * u + ka;
+                const int64_t row = int64_t(j < nz ? j : nz - 1) * g.ng;
+                load4<kVec>(w0 + row, mm, g.ng, a0[u]);
+                load4<kVec>(w1 + row, mm, g.ng, a1[u]);
+                const double bj = lr[j < nz ? j : nz - 1];
+                b[u] = j < nz && take ? bj : 0.0;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[u], b[u], d0, 0, 0, 0);
-                d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[u], b[u], d1, 0, 0, 0);
-            }
+            for (int u = 0; u < kStep; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    d[0][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a0[u][q]), b[u], d[0][q], 0, 0, 0);
+                    d[1][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a1[u][q]), b[u], d[1][q], 0, 0, 0);
+                }
         }
-        int nxt = ik > cur ? ik : 0x7fffffff;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) nxt = min(nxt, __shfl_xor(nxt, off, 64));
-        cur = nxt;
+        cur = wave_min(ik > cur ? ik : 0x7fffffff);
     }
-    // lane l holds rows m0 + 4 i + ka of column col
-    if (r < 0) return;
-    R* o = out + r * 2 * g.ng;
+    // Add the waves' sums in wave order, half a table row at a time
+    // (h: elements i = 2 h, 2 h + 1): wave w finishes element 2 h + (w & 1) of
+    // chains 2 (w >> 1) and 2 (w >> 1) + 1, two consecutive nodes.
+    static_assert(kPvWaves == 4, "the split of the finishing work");
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + 4 * i + ka;
-        if (m < g.ng) {
-            o[m] = R(d0[i]);
-            o[g.ng + m] = R(d1[i]);
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (s + h) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    lds[((wave * 2 + i) * 4 + q) * 64 + lane] = d[s][q][2 * h + i];
+            __syncthreads();
+            const int i = wave & 1, q0 = wave >> 1 << 1;
+            const int m = m0 + 4 * (4 * (2 * h + i) + ka) + q0;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                double v = lds[(i * 4 + q0 + q) * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < kPvWaves; ++w) v += lds[((w * 2 + i) * 4 + q0 + q) * 64 + lane];
+                if (r >= 0 && m + q < g.ng) out[r * 2 * g.ng + s * g.ng + m + q] = R(v);
+            }
         }
+}
+
+// One sorted row, one node per lane: wave w takes part w % kRowSplit of the
+// bins of the 64 nodes at m0 + 64 (w / kRowSplit), and the parts are added in
+// order.  What bounds it is the traffic of the distinct W rows into the eight
+// L2s (53 MB in float, 106 MB in FP64 for a population of 512): the split and
+// the loads in flight only have to keep that busy (float 18.2 us unsplit with
+// 40 loads in flight, 20.0 split by 4; FP64 45.9 and 42.0).
+template <typename WT>
+constexpr int kRowSplit = sizeof(WT) == 4 ? 1 : 4;
+template <typename WT>
+constexpr int kRowNodes = kPvNodes * kPvWaves / kRowSplit<WT>;   // per workgroup
+template <typename R, typename WT>
+__device__ inline void pv_tables_row(const WT* __restrict__ W, const double* __restrict__ ldp,
+                                     const PvOrder& ord, int64_t pos, int32_t nz,
+                                     const GridDev& g, R* __restrict__ out, int m0,
+                                     double* __restrict__ lds) {
+    constexpr int kSplit = kRowSplit<WT>;
+    const int64_t r = ord.perm[pos];
+    const int ik = ord.key[pos];
+    const int mlo = ord.mlo[r];
+    if (mlo >= m0 + kRowNodes<WT>) return;             // uniform
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int part = wave % kSplit;
+    const int mw = m0 + wave / kSplit * kPvNodes, m = mw + lane;
+    double a0 = 0.0, a1 = 0.0;
+    if (mw < g.ng && mlo < mw + kPvNodes) {
+        const WT* w0 = W + int64_t(ik) * nz * g.ng + (m < g.ng ? m : 0);
+        const WT* w1 = w0 + int64_t(nz) * g.ng;
+        const double* lr = ldp + r * nz;           // uniform
+        const int per = (nz + kSplit - 1) / kSplit;
+        const int j1 = min(nz, per * (part + 1));
+        constexpr int kStep = kSplit == 1 ? 20 : 9;     // bins in flight
+        int j = per * part;
+        for (; j + kStep <= j1; j += kStep) {
+            WT x0[kStep], x1[kStep];
+#pragma unroll
+            for (int b = 0; b < kStep; ++b) {
+                x0[b] = w0[int64_t(j + b) * g.ng];
+                x1[b] = w1[int64_t(j + b) * g.ng];
+            }
+#pragma unroll
+            for (int b = 0; b < kStep; ++b) {
+                a0 += double(x0[b]) * lr[j + b];
+                a1 += double(x1[b]) * lr[j + b];
+            }
+        }
+        for (; j < j1; ++j) {
+            a0 += double(w0[int64_t(j) * g.ng]) * lr[j];
+            a1 += double(w1[int64_t(j) * g.ng]) * lr[j];
+        }
+    }
+    if constexpr (kSplit > 1) {
+        if (part > 0) {
+            lds[wave * 128 + lane] = a0;
+            lds[wave * 128 + 64 + lane] = a1;
+        }
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int w = 1; w < kSplit; ++w) {
+            a0 += lds[(wave + w) * 128 + lane];
+            a1 += lds[(wave + w) * 128 + 64 + lane];
+        }
+    }
+    if (m < g.ng && mlo < mw + kPvNodes) {
+        R* o = out + r * 2 * g.ng + m;
+        o[0] = R(a0);
+        o[g.ng] = R(a1);
     }
 }
 
-// One launch for both: blocks [0, n_mfma) take matrix-core tiles, the
-// others the per-row work (n_mfma is a multiple of the XCD count, so the
-// per-row blocks keep their XCD-aware order).  Each row is written by
-// exactly one of the two, as the same test on the sorted keys decides.
-template <typename R, typename WT>
-__global__ __launch_bounds__(kBlock) void k_pv_tables(const WT* __restrict__ W,
+// Workgroups [0, n_mfma) take (tile, 64 nodes) on the matrix cores, the
+// others (sorted row, 64 nodes): those in an XCD-aware order -- blocks go
+// round-robin to the eight XCDs, so block p works on item (p mod 8) *
+// (blocks / 8) + p / 8 (rounded for a remainder; n_mfma is a multiple of 8)
+// and each XCD walks a contiguous stretch of the sorted rows, whose W rows
+// its L2 then serves to the following rows of equal ik.
+constexpr int kXcds = 8;
+template <bool kVec, typename R, typename WT>
+__global__ __launch_bounds__(kBlock, 3) void k_pv_tables(const WT* __restrict__ W,
                                                       const double* __restrict__ ldp,
-                                                      const int32_t* __restrict__ ikr,
-                                                      const int32_t* __restrict__ perm,
-                                                      int64_t nr, int32_t nz, GridDev g,
-                                                      int64_t n_mfma, R* __restrict__ out) {
-    __shared__ double lp[4096];
-    const int64_t b = blockIdx.x;
+                                                      PvOrder ord, int64_t nr, int32_t nz,
+                                                      GridDev g, int64_t n_mfma,
+                                                      int64_t blocks, R* __restrict__ out) {
+    __shared__ double lds[kPvLds];
+    const int64_t b = flat_block();
+    if (b >= blocks) return;
+    const int nmb = (g.ng + kPvNodes - 1) / kPvNodes;
     if (b < n_mfma) {
-        pv_tables_mfma<R, WT>(W, ldp, ikr, perm, nr, nz, g, out, b);
+        const int64_t rt = b / nmb;
+        if (rt * kTileRows >= nr || !ord.mfma[rt]) return;
+        pv_tables_mfma<kVec, R, WT>(W, ldp, ord, nr, nz, g, out, rt, int(b - rt * nmb) * kPvNodes, lds);
         return;
     }
-    pv_tables_rows<R, WT>(W, ldp, ikr, perm, nz, g, out, int64_t(gridDim.x) - n_mfma,
-                          b - n_mfma, lp);
+    const int64_t nb = blocks - n_mfma, p = b - n_mfma;
+    const int64_t q = nb / kXcds, rem = nb % kXcds, x = p % kXcds;
+    const int64_t L = (x < rem ? x * (q + 1) : rem * (q + 1) + (x - rem) * q) + p / kXcds;
+    const int nrb = (g.ng + kRowNodes<WT> - 1) / kRowNodes<WT>;
+    const int64_t pos = L / nrb;
+    if (ord.mfma[pos / kTileRows]) return;
+    pv_tables_row<R, WT>(W, ldp, ord, pos, nz, g, out, int(L - pos * nrb) * kRowNodes<WT>, lds);
 }
 
 // Direct model (Sect. 3.1.1): the LD-weighted vector of row r = (vector,
@@ -487,8 +566,10 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
     double* edge = direct_lds;                     // edges 1 .. nz - 1, at j - 1
     double* dl = direct_lds + (nz - 1);            // l_j - l_{j-1}, at j - 1
     const int nmb = (g.ng + 63) / 64;
-    const int64_t r = int64_t(blockIdx.x) % nr;
-    const int mb = nmb - 1 - int(int64_t(blockIdx.x) / nr);
+    const int64_t b = flat_block();
+    if (b >= nr * nmb) return;
+    const int64_t r = b % nr;
+    const int mb = nmb - 1 - int(b / nr);
     const int64_t ipv = r / g.npb;
     const int pb = int(r - ipv * g.npb);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -612,8 +693,7 @@ hipError_t launch_direct_rows(const rr_tables* t, const double* pv, int32_t npv,
     const GridDev g = grid_dev(t);
     const int64_t nr = int64_t(npv) * t->npb;
     const int64_t blocks = nr * ((g.ng + 63) / 64);
-    if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    const dim3 grid{unsigned(blocks)};
+    const dim3 grid = flat_grid(blocks);
     // the edges and profile steps (65 520 B at the largest nz), then the waves' sums
     const size_t lds = sizeof(double) * std::max<size_t>(2 * size_t(t->nz - 1),
                                                          64 * (kDirectWaves - 1));
@@ -734,30 +814,37 @@ hipError_t launch_small_planet_rows(const rr_tables* t, const double* pv, int32_
 
 hipError_t launch_pv_ld(const rr_tables* t, const double* prof, const double* pv,
                         int32_t npv, int32_t npar, int32_t precision, double* ldp,
-                        double* istar, double* inv_istar, int32_t* ikr, int32_t* perm,
-                        void* rows, hipStream_t s, bool w32) {
+                        double* istar, double* inv_istar, const PvOrder& ord,
+                        void* rows, hipStream_t s, bool w32, PvConst* pvc) {
     const GridDev g = grid_dev(t);
     const int64_t nr = int64_t(npv) * t->npb;     // (vector, passband) rows
-    hipLaunchKernelGGL(k_pv_prep, dim3(unsigned(nr + 1)), dim3(kBlock), 0, s, t->mu_s, prof,
-                       t->nmu, t->zm, t->nz, pv, npv, npar, g, ldp, istar, inv_istar, ikr, perm);
+    hipLaunchKernelGGL(precision == RR_FP64 ? k_pv_prep<false> : k_pv_prep<true>,
+                       dim3(unsigned(nr + 1)), dim3(kBlock), 0, s, t->mu_s, prof, t->nmu, t->zm,
+                       t->nz, pv, npv, npar, g, ldp, istar, inv_istar, ord, t->grid.k1, pvc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // matrix-core tiles rounded up to whole rounds of the XCDs, then the
-    // per-row blocks; both parts read the same weights (FP64, or the FP32
-    // copy with w32), so a row's values do not depend on which part took it
-    const int64_t n_mfma = ((nr + 15) / 16 * ((g.ng + 63) / 64) + kXcds - 1) / kXcds * kXcds;
-    const int64_t n_rows = nr * ((g.ng + kBlock - 1) / kBlock);
-    if (n_mfma + n_rows >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    const dim3 grid(unsigned(n_mfma + n_rows));
+    // both parts read the same weights (FP64, or the FP32 copy with w32)
+    const int64_t nmb = (g.ng + kPvNodes - 1) / kPvNodes;
+    const int64_t n_mfma =
+        ((nr + kTileRows - 1) / kTileRows * nmb + kXcds - 1) / kXcds * kXcds;
+    const int64_t row_nodes = precision != RR_FP64 && w32 ? kRowNodes<float> : kRowNodes<double>;
+    const int64_t blocks = n_mfma + nr * ((g.ng + row_nodes - 1) / row_nodes);
+    const dim3 grid = flat_grid(blocks);
+    // 16-byte loads of W need rows of a multiple of 4 nodes
+    auto launch = [&](auto kernel, const auto* W, auto* out) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, s, W, ldp, ord, nr, t->nz, g, n_mfma,
+                           blocks, out);
+    };
+    const bool vec = g.ng % 4 == 0;
     if (precision == RR_FP64)
-        hipLaunchKernelGGL((k_pv_tables<double, double>), grid, dim3(kBlock), 0, s, t->W, ldp,
-                           ikr, perm, nr, t->nz, g, n_mfma, static_cast<double*>(rows));
+        launch(vec ? k_pv_tables<true, double, double> : k_pv_tables<false, double, double>, t->W,
+               static_cast<double*>(rows));
     else if (w32)
-        hipLaunchKernelGGL((k_pv_tables<float, float>), grid, dim3(kBlock), 0, s, t->W32, ldp,
-                           ikr, perm, nr, t->nz, g, n_mfma, static_cast<float*>(rows));
+        launch(vec ? k_pv_tables<true, float, float> : k_pv_tables<false, float, float>, t->W32,
+               static_cast<float*>(rows));
     else
-        hipLaunchKernelGGL((k_pv_tables<float, double>), grid, dim3(kBlock), 0, s, t->W, ldp,
-                           ikr, perm, nr, t->nz, g, n_mfma, static_cast<float*>(rows));
+        launch(vec ? k_pv_tables<true, float, double> : k_pv_tables<false, float, double>, t->W,
+               static_cast<float*>(rows));
     return hipGetLastError();
 }
 
