@@ -683,7 +683,9 @@ class RRLogLik(torch.autograd.Function):
         gpv = gout[:, None] * g
         gprof = gist = None
         if ctx.want_prof or ctx.want_ist:
-            if bool(torch.all(gout == gout[0])):
+            # equal weights: known from a broadcast gradient (logl.sum()), whose
+            # one element every row shares, without waiting for the device
+            if gout.stride(0) == 0 or bool(torch.all(gout == gout[0])):
                 gprof = gp * gout[0] if ctx.want_prof else None
                 gist = gi * gout[0] if ctx.want_ist else None
             else:

@@ -200,7 +200,12 @@ struct rr_tables {
     // ordered, so a stream's buffer is reused without waiting).
     std::mutex ws_mu;
     std::unordered_map<hipStream_t, std::pair<void*, size_t>> ws;
-
+    // The same for the log-likelihood (a call's buffer is its own until the
+    // work that uses it is enqueued: lk_mu is held meanwhile), each of at most
+    // kKeepBytes and together at most kKeepTotal.
+    std::mutex lk_mu;
+    std::unordered_map<hipStream_t, std::pair<void*, size_t>> lk;
+    size_t lk_total = 0;
 };
 
 namespace rr {
@@ -222,6 +227,7 @@ inline void launch_timed(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_
         hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
 }
 int hip_fail(hipError_t err, const char* what);
+constexpr size_t kKeepBytes = size_t(96) << 20, kKeepTotal = size_t(512) << 20;
 // Device workspace of at least `bytes` for `stream`, owned by the tables.
 hipError_t stream_workspace(rr_tables* t, hipStream_t stream, size_t bytes, void** out);
 rr::GridDev grid_dev(const rr_tables* t);
