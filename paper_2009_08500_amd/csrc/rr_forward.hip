@@ -898,26 +898,30 @@ SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision
     // Two regimes, from sweeps of both precisions over the population
     // workloads (16 to 4096 rows, 1000 to 50 000 times, 1 to 16 transit
     // workgroups per row, 4 to 16 rows per streaming workgroup).  With
-    // `ref` the float fused kernel's resident workgroups (4096 here; the
-    // double kernel holds half as many, yet measured best with the same
-    // counts):
+    // `ref` the float fused kernel's resident workgroups (5120 here), and for
+    // the double kernel, which holds 2048, and for 768 rows or more twice the
+    // double kernel's (256 x 50 000 in float: 20.3 us with 5120, 21.7 with
+    // 4096; 1024 x 20 000 25.0 and 23.1, 1024 x 10 000 in double 29.6 and
+    // 27.5):
     //  * every workgroup derives its rows' constants itself and no setup
-    //    launch precedes the kernel, as long as that launch has at most
-    //    2 ref workgroups; beyond that too many of them pay the set-up's
-    //    latency again behind the first.  Transit workgroups per row:
-    //    ceil(sqrt(2 ref x min(tiles, 40) / (40 rows))), fewer for series
-    //    shorter than 40 tiles (20 000 exposures), whose rows have fewer
-    //    transits, and at least 1024 in all; over 40 tiles or more that is
-    //    16 per row at 64 rows, 8 at 128, 6 at 256, 4 at 512, 3 at 1024.
-    //    More queue behind each other or spend their time on set-up, fewer
-    //    leave too much serial work per lane.  From 768 rows over 32 tiles
-    //    or more the streaming workgroups take 8 rows, so that fewer of
-    //    them pay the set-up.
+    //    launch precedes the kernel, as long as that launch has at most four
+    //    times the double kernel's resident workgroups (8192); beyond that
+    //    too many of them pay the set-up's latency again behind the first.
+    //    Transit workgroups per row: ceil(sqrt(2 ref x min(tiles, 40) /
+    //    (40 rows))), fewer for series shorter than 40 tiles (20 000
+    //    exposures), whose rows have fewer transits, and at least 1024 in
+    //    all; over 40 tiles or more that is 16 per row at 64 rows and, with
+    //    5120 and 4096, 9 and 8 at 128, 7 and 6 at 256, 5 and 4 at 512; 3 at
+    //    1024.  More queue behind each other or spend their time on set-up,
+    //    fewer leave too much serial work per lane.  From 768 rows over 32
+    //    tiles or more the streaming workgroups take 8 rows, so that fewer
+    //    of them pay the set-up.
     //  * otherwise the setup kernel runs first and, for 512 rows or more
     //    over 16 tiles or more, there are as many transit workgroups as are
     //    resident at once, else at most 2048.
-    const int ref = split_capacity(RR_MIXED, true);
-    if (cap_self > 0 && ref > 0) {
+    const int cap_double = split_capacity(RR_FP64, true);
+    const int ref = npv >= 768 ? 2 * cap_double : std::max(cap_self, 2 * cap_double);
+    if (cap_self > 0 && cap_double > 0) {
         const double len = double(std::min<int64_t>(ntiles, 40));
         const int64_t by_rows =
             int64_t(std::ceil(std::sqrt(2.0 * double(ref) * len / (40.0 * double(npv)))));
@@ -927,7 +931,7 @@ SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision
         const int32_t rows =
             npv >= 768 && ntiles >= 32 ? std::min<int32_t>(2 * kSplitRows, npv) : sp.rows_per;
         const int64_t blocks = int64_t(npv) * shares + ntiles * ((npv + rows - 1) / rows);
-        if (blocks <= 2 * int64_t(ref)) {
+        if (blocks <= 4 * int64_t(cap_double)) {
             sp.self_setup = true;
             sp.shares = int32_t(shares);
             sp.rows_per = rows;
