@@ -697,15 +697,43 @@ __global__ __launch_bounds__(kFwdBlock) void k_forward_split(FwdJob job, LcInfo 
     stream_rows<R, kTimesPerThread, kSelf>(job, lc, si, r0, r1, u - rg * job.ntiles);
 }
 
-// One population (rr_evaluate): workgroup (x, y) -> row pv0 + y, tile x of
-// 64 J times.  kSubPar: some light curve has nss > 1.
+// The light curves' description in LDS, one light curve per lane: indexed
+// per lane from the kernel arguments, every read would be a trip to memory.
+__device__ inline const LcInfo& stage_lc(const LcInfo& lc, LcInfo* lds) {
+    const int lane = threadIdx.x & 63;
+    static_assert(RR_MAX_LC <= 64 && kFwdBlock == 64, "one light curve per lane");
+    if (lane < RR_MAX_LC) {
+        lds->pb[lane] = lc.pb[lane];
+        lds->nss[lane] = lc.nss[lane];
+        lds->exptime[lane] = lc.exptime[lane];
+        if (lane == 0) lds->nlc = lc.nlc;
+    }
+    __syncthreads();
+    return *lds;
+}
+
+// One population (rr_evaluate): row pv0 + r, tile x of 64 J times.  kSubPar:
+// some light curve has nss > 1.  Within a run of job.row_run rows the rows run
+// fastest (see launch_forward).
 template <typename R, bool kSubPar, int J>
 __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdJob job, LcInfo lc, GridDev g,
                                                     const R* __restrict__ T,
                                                     const double* __restrict__ inv_istar) {
-    const int ipv = job.pv0 + blockIdx.y;
-    const int tile = blockIdx.x;
-    forward_block<R, kSubPar, J>(job, lc, ipv, tile, g, T, inv_istar);
+    const int64_t b = flat_block();
+    const int64_t per = int64_t(job.row_run) * job.ntiles;    // workgroups of a run of rows
+    const int r0 = int(b / per) * job.row_run;
+    if (r0 >= job.npv) return;
+    const int rows = min(job.row_run, job.npv - r0);
+    const int local = int(b - int64_t(r0) * job.ntiles);
+    const int tile = local / rows;
+    if (tile >= job.ntiles) return;
+    const int ipv = job.pv0 + r0 + (local - tile * rows);
+    if constexpr (kSubPar) {
+        __shared__ LcInfo slc;
+        forward_block<R, true, J>(job, stage_lc(lc, &slc), ipv, tile, g, T, inv_istar);
+    } else {
+        forward_block<R, false, J>(job, lc, ipv, tile, g, T, inv_istar);
+    }
 }
 
 // Grouped launch (serving): workgroup b belongs to the last job whose
@@ -825,21 +853,28 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
     for (int l = 0; l < lc.nlc; ++l) job.max_nss = lc.nss[l] > job.max_nss ? lc.nss[l] : job.max_nss;
     const KernelEvents ev = kernel_events();
     const bool sub = job.max_nss > 1;
-    // rows along grid y, at most 65535 per launch
-    for (int32_t r0 = 0; r0 < npv; r0 += 65535) {
-        job.pv0 = r0;
-        const dim3 grid(unsigned(job.ntiles), unsigned(npv - r0 < 65535 ? npv - r0 : 65535));
-        const dim3 block(kFwdBlock);
-        hipEvent_t st = r0 == 0 ? ev.before : nullptr;
-        hipEvent_t sp = npv - r0 <= 65535 ? ev.after : nullptr;
-        const hipError_t e =
-            precision == RR_FP64
-                ? launch_forward_j<double>(J, sub, grid, block, s, st, sp, job, lc, g, t->T64,
-                                           t->inv_istar)
-                : launch_forward_j<float>(J, sub, grid, block, s, st, sp, job, lc, g, t->T32,
-                                          t->inv_istar);
-        if (e != hipSuccess) return e;
-    }
+    // Order of the workgroups: 256 rows of one tile, then of the next, while
+    // the launch is at most about three rounds of resident waves.  A series'
+    // long exposures, whose tiles hold the most flagged subsamples, then start
+    // first for every row where they come first in it, and the last tiles to
+    // start, whose transits are the launch's tail, belong to many rows (256
+    // rows of two light curves at nss 10 and two at nss 1: 35.9 -> 30.5 us per
+    // call in float, 49.2 -> 43.0 in FP64; 512 x 20 000 at nss 1, with the rows
+    // of the small-planet model: 24.9 -> 23.8, 33.2 -> 30.9).  Larger launches
+    // write more rows at a time than suits memory: 64 rows at nss 1 (512 x
+    // 60 000: 38.5 -> 36.7, 64.6 -> 57.8; with 256 rows FP64 takes 66.1), and
+    // row by row when supersampled, where tiles of all kinds mixed serve better
+    // (512 rows at nss 5: 38.9 and 67.1; with 64 rows 38.7 and 71.5).
+    const int64_t waves = int64_t(job.ntiles) * npv;
+    job.row_run = waves <= 24576 ? 256 : (sub ? 1 : 64);
+    const dim3 grid = flat_grid(waves), block(kFwdBlock);
+    const hipError_t e =
+        precision == RR_FP64
+            ? launch_forward_j<double>(J, sub, grid, block, s, ev.before, ev.after, job, lc, g,
+                                       t->T64, t->inv_istar)
+            : launch_forward_j<float>(J, sub, grid, block, s, ev.before, ev.after, job, lc, g,
+                                      t->T32, t->inv_istar);
+    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 

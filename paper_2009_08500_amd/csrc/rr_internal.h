@@ -79,6 +79,7 @@ struct FwdJob {
     const double* inv_istar_pv;   // NULL: the tables' 1/I_star
     int32_t ldw_exact_k;          // 1: ldw_pv rows are for the row's exact k (direct model)
     int32_t spread;               // 1: supersampled exposures may spread over lanes
+    int32_t row_run;              // rows whose equal tiles are neighbours in the launch
 };
 // Forward-kernel variants (rr_evaluate_variant): exposures per lane
 // J = 4, 8, 16 for v = 0, 1, 2 with subsamples spread over lanes where
