@@ -244,9 +244,14 @@ __global__ __launch_bounds__(kBlock) void k_adj_prep(
 // per-vector sums.
 //   use_ring 0 (tables that leave no LDS for the ring): a block's flagged
 // exposures are evaluated where they stand.
+//   Float is held to 128 vector registers (130 with the profile gradient and
+// one passband when left alone, no spills; 142 with four, five dwords spilled)
+// for four waves per SIMD: 1024 walkers x 50 000 x 5 with a profile per row and
+// its gradient 127 -> 91 us, 207 -> 165 a call; 1024 x 92 160 over four
+// passbands with the profile gradient 361 -> 257 a call.
 constexpr int kRing = 128;                    // exposures; at most 127 are held
 template <typename R, int NPBT, bool kProf>
-__global__ __launch_bounds__(kAdjBlock) void k_adjoint(
+__global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) void k_adjoint(
     const double* __restrict__ times, const int32_t* __restrict__ lcids,
     int32_t npt, LcInfo lc, const double* __restrict__ pv, int32_t npar,
     const PvConst* __restrict__ pvc, GridDev g, const R* __restrict__ T,

@@ -828,19 +828,21 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
     const GridDev g = grid_dev(t);
     const int32_t nblk = int32_t((int64_t(npt) + kTimeBlock - 1) / kTimeBlock);
     // Workgroups per vector (of two waves): as many waves as the kernel's
-    // registers let the chip hold at once -- 4 per SIMD in float without the
-    // profile gradient, else 2 -- since more parts only cost each row more
-    // half-filled last batches (1024 walkers x 50 000 x 5, us per call at
-    // 2048 / 4096 / 8192 waves: float 92 / 81 / 107, FP64 152 / 198 / 231,
-    // FP64 with the profile gradient 632 / 693 / 749); each wave with at
-    // least 16 time blocks to look through, and with the profile gradient at
-    // most 256 MiB of per-workgroup partials.
-    const int64_t waves = !prof && precision == RR_MIXED ? 4096 : 2048;
+    // registers let the chip hold at once -- 4 per SIMD in float, 2 in FP64 --
+    // since more parts only cost each row more half-filled last batches (1024
+    // walkers x 50 000 x 5, us per call at 2048 / 4096 / 8192 waves: float
+    // 92 / 81 / 107, FP64 152 / 198 / 231; the kernel alone with the profile
+    // gradient, float 107 / 91 / -, FP64 143 / 207 / -); each wave with at
+    // least 16 time blocks to look through; with the profile gradient, whose
+    // parts are summed again, 2048 below 16 384 exposures (1024 walkers x 5000:
+    // 75.6 us, 80.5 with 4096), at most 16 parts (64 walkers x 50 000 x 5 in
+    // float: 75.5 us with 16, 81 with 25) and 256 MiB of partials.
+    const int64_t waves = precision == RR_MIXED && !(prof && nblk < 256) ? 4096 : 2048;
     int64_t nseg = (waves + 2 * int64_t(npv) - 1) / (2 * int64_t(npv));
     nseg = std::min<int64_t>(nseg, (int64_t(nblk) + 31) / 32);
     if (prof) {
         const size_t row_bytes = sizeof(double) * size_t(t->npb) * (size_t(g.ng) + 1);
-        nseg = std::min<int64_t>(nseg, int64_t((size_t(256) << 20) / (row_bytes * npv)));
+        nseg = std::min<int64_t>({nseg, 16, int64_t((size_t(256) << 20) / (row_bytes * npv))});
     }
     nseg = std::max<int64_t>(nseg, 1);
     // one buffer for every temporary

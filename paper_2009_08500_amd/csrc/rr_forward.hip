@@ -677,12 +677,15 @@ __device__ inline void transit_share(const FwdJob& job, const LcInfo& lc, const 
 // of rows (tile u % ntiles of rows [rows_per u / ntiles, ...)).  The
 // transit workgroups are resident from the start, so their work runs beside
 // the streaming stores instead of forming a tail.  kSelf: each workgroup
-// derives its rows' constants itself (no setup launch before it).
+// derives its rows' constants itself (no setup launch before it).  FP64 is
+// held to 168 vector registers (175 when left alone, without spills either
+// way): three waves per SIMD instead of two hide more of the serial chains
+// (us per call, FP64: 512 x 20 000 24.7 -> 21.6, 1024 x 10 000 27.5 -> 23.3,
+// 4096 x 5000 53.8 -> 49.3).
 template <typename R, bool kSelf>
-__global__ __launch_bounds__(kFwdBlock) void k_forward_split(FwdJob job, LcInfo lc, GridDev g,
-                                                          const R* __restrict__ T,
-                                                          const double* __restrict__ inv_istar,
-                                                          SplitInfo si) {
+__global__ __launch_bounds__(kFwdBlock, sizeof(R) == 8 ? 3 : 1) void k_forward_split(
+    FwdJob job, LcInfo lc, GridDev g, const R* __restrict__ T,
+    const double* __restrict__ inv_istar, SplitInfo si) {
     const int b = int(blockIdx.x);
     const int n2 = job.npv * si.shares;
     if (b < n2) {
@@ -879,19 +882,22 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
 }
 
 // Workgroups of the split kernel (one wave each) resident at once on the
-// current device; 0 if the query fails.
-static int split_capacity(int32_t precision, bool self) {
+// current device, and its CUs; both 0 if the query fails.
+struct SplitCapacity {
+    int resident, cus;
+};
+static SplitCapacity split_capacity(int32_t precision, bool self) {
     static std::mutex mu;
-    static std::map<std::tuple<int, int, int>, int> cache;
+    static std::map<std::tuple<int, int, int>, SplitCapacity> cache;
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipGetDevice(&dev) != hipSuccess) return {0, 0};
     const auto key = std::make_tuple(dev, precision == RR_FP64 ? 0 : 1, self ? 1 : 0);
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
     int ncu = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
+        return {0, 0};
     hipError_t e;
     if (precision == RR_FP64)
         e = self ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -903,9 +909,8 @@ static int split_capacity(int32_t precision, bool self) {
                        &per_cu, k_forward_split<float, true>, kFwdBlock, 0)
                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(
                        &per_cu, k_forward_split<float, false>, kFwdBlock, 0);
-    if (e != hipSuccess || per_cu <= 0) return 0;
-    cache[key] = per_cu * ncu;
-    return per_cu * ncu;
+    if (e != hipSuccess || per_cu <= 0) return {0, 0};
+    return cache[key] = {per_cu * ncu, ncu};
 }
 
 bool split_preferred(const rr_tables* t, const rr_series* se, int32_t npv, int32_t precision) {
@@ -915,14 +920,13 @@ bool split_preferred(const rr_tables* t, const rr_series* se, int32_t npv, int32
     // 1024 rows; the per-tile kernel stays ahead on supersampled series.
     const int64_t ntiles = (int64_t(se->npt) + kFwdTile - 1) / kFwdTile;
     if (se->max_nss != 1 || (ntiles <= 2 && npv > 1024)) return false;
-    return split_capacity(precision, false) > 0;
+    return split_capacity(precision, false).resident > 0;
 }
 
 SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision) {
     SplitPlan sp;
-    int cap = split_capacity(precision, false);
+    int cap = split_capacity(precision, false).resident;
     if (cap <= 0) cap = 2048;
-    const int cap_self = split_capacity(precision, true);
     const int64_t ntiles = (int64_t(se->npt) + kFwdTile - 1) / kFwdTile;
     const int64_t tiles_total = ntiles * npv;
     const int64_t max_sh = std::max<int64_t>(1, (int64_t(se->npt) + 63) / 64);
@@ -933,20 +937,21 @@ SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision
     // Two regimes, from sweeps of both precisions over the population
     // workloads (16 to 4096 rows, 1000 to 50 000 times, 1 to 16 transit
     // workgroups per row, 4 to 16 rows per streaming workgroup).  With
-    // `ref` the float fused kernel's resident workgroups (5120 here), and for
-    // the double kernel, which holds 2048, and for 768 rows or more twice the
-    // double kernel's (256 x 50 000 in float: 20.3 us with 5120, 21.7 with
-    // 4096; 1024 x 20 000 25.0 and 23.1, 1024 x 10 000 in double 29.6 and
-    // 27.5):
+    // `ref` 20 workgroups per CU, the float kernel's resident ones, and from
+    // 512 rows in FP64 the 12 per CU of the double kernel, from 768 rows in
+    // float 16 per CU (us per call, rows x times: FP64 at 12 / 16 / 20 per CU
+    // 256 x 50 000 31.7 / 28.4 / 27.2, 512 x 20 000 21.6 / 21.7 / 22.6,
+    // 768 x 20 000 32.5 / 35.6 / 35.5; float 256 x 50 000 - / 21.7 / 20.3,
+    // 768 x 20 000 20.2 / 18.0 / 18.1, 1024 x 20 000 23.1 / 23.1 / 25.0):
     //  * every workgroup derives its rows' constants itself and no setup
-    //    launch precedes the kernel, as long as that launch has at most four
-    //    times the double kernel's resident workgroups (8192); beyond that
+    //    launch precedes the kernel, as long as that launch has at most 32
+    //    workgroups per CU; beyond that
     //    too many of them pay the set-up's latency again behind the first.
     //    Transit workgroups per row: ceil(sqrt(2 ref x min(tiles, 40) /
     //    (40 rows))), fewer for series shorter than 40 tiles (20 000
     //    exposures), whose rows have fewer transits, and at least 1024 in
-    //    all; over 40 tiles or more that is 16 per row at 64 rows and, with
-    //    5120 and 4096, 9 and 8 at 128, 7 and 6 at 256, 5 and 4 at 512; 3 at
+    //    all; over 40 tiles or more that is 16 per row at 64 rows, 9 at 128,
+    //    7 at 256, 5 (FP64 4) at 512, 4 (FP64 3) at 768 and 3 at
     //    1024.  More queue behind each other or spend their time on set-up,
     //    fewer leave too much serial work per lane.  From 768 rows over 32
     //    tiles or more the streaming workgroups take 8 rows, so that fewer
@@ -954,9 +959,11 @@ SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision
     //  * otherwise the setup kernel runs first and, for 512 rows or more
     //    over 16 tiles or more, there are as many transit workgroups as are
     //    resident at once, else at most 2048.
-    const int cap_double = split_capacity(RR_FP64, true);
-    const int ref = npv >= 768 ? 2 * cap_double : std::max(cap_self, 2 * cap_double);
-    if (cap_self > 0 && cap_double > 0) {
+    const int cus = split_capacity(precision, true).cus;
+    const int full = cus * 20;
+    const int ref = precision == RR_FP64 ? (npv >= 512 ? cus * 12 : full)
+                                         : (npv >= 768 ? cus * 16 : full);
+    if (cus > 0) {
         const double len = double(std::min<int64_t>(ntiles, 40));
         const int64_t by_rows =
             int64_t(std::ceil(std::sqrt(2.0 * double(ref) * len / (40.0 * double(npv)))));
@@ -966,7 +973,7 @@ SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision
         const int32_t rows =
             npv >= 768 && ntiles >= 32 ? std::min<int32_t>(2 * kSplitRows, npv) : sp.rows_per;
         const int64_t blocks = int64_t(npv) * shares + ntiles * ((npv + rows - 1) / rows);
-        if (blocks <= 4 * int64_t(cap_double)) {
+        if (blocks <= 32 * int64_t(cus)) {
             sp.self_setup = true;
             sp.shares = int32_t(shares);
             sp.rows_per = rows;
