@@ -459,8 +459,11 @@ __device__ inline PvConst split_row_const(const FwdJob& job, const SplitInfo& si
 // per exposure and its stores.  On the aligned path (whole
 // tile in one light curve, 16-B aligned rows) lane L owns the kVec
 // consecutive exposures 64 kVec q + kVec L + v of group q and stores a
-// group with one 16-B store when none of it is in the window.
-template <typename R, int J, bool kSelf>
+// group with one 16-B store when none of it is in the window.  kBypass: a
+// group none of whose lanes has an exposure in the window is stored past the
+// caches (plan_forward_split); the others' lines are shared with the transit
+// workgroups.
+template <typename R, int J, bool kSelf, bool kBypass>
 __device__ inline void stream_rows(const FwdJob& job, const LcInfo& lc, const SplitInfo& si,
                                    int r0, int r1, int tile) {
     constexpr int kSpan = 64 * J;
@@ -544,8 +547,11 @@ __device__ inline void stream_rows(const FwdJob& job, const LcInfo& lc, const Sp
                     in[v] = win_in(win_phase(tv[q * kVec + v], invP, w), w);
                     any = any || in[v];
                 }
-                if (!any) {
-                    *reinterpret_cast<RV*>(orow + base) = RV(R(1));
+                RV* ov = reinterpret_cast<RV*>(orow + base);
+                if (kBypass && !__any(any)) {
+                    __builtin_nontemporal_store(RV(R(1)), ov);
+                } else if (!any) {
+                    *ov = RV(R(1));
                 } else {
 #pragma unroll
                     for (int v = 0; v < kVec; ++v)
@@ -672,32 +678,45 @@ __device__ inline void transit_share(const FwdJob& job, const LcInfo& lc, const 
     }
 }
 
-// The split launch: workgroups [0, npv * shares) take the transits (share
-// b % shares of row b / shares); the others stream time tiles over blocks
-// of rows (tile u % ntiles of rows [rows_per u / ntiles, ...)).  The
-// transit workgroups are resident from the start, so their work runs beside
-// the streaming stores instead of forming a tail.  kSelf: each workgroup
-// derives its rows' constants itself (no setup launch before it).  FP64 is
-// held to 168 vector registers (175 when left alone, without spills either
-// way): three waves per SIMD instead of two hide more of the serial chains
-// (us per call, FP64: 512 x 20 000 24.7 -> 21.6, 1024 x 10 000 27.5 -> 23.3,
-// 4096 x 5000 53.8 -> 49.3).
-template <typename R, bool kSelf>
+// The split launch: npv * shares workgroups take the transits (number n the
+// share n % shares of row n / shares); the others stream time tiles over
+// blocks of rows (number u the tile u % ntiles of rows [rows_per u / ntiles,
+// ...)).  The transit workgroups come first and are resident from the start,
+// so their work runs beside the streaming stores instead of forming a tail;
+// with kLarge the two kinds alternate (plan_forward_split) in eights, so that
+// each kind spreads over the eight XCDs.  kSelf: each workgroup derives its
+// rows' constants itself (no setup launch before it).  FP64 is held to 168
+// vector registers (175 when left alone, without spills either way): three
+// waves per SIMD instead of two hide more of the serial chains (us per call,
+// FP64: 512 x 20 000 24.7 -> 21.6, 1024 x 10 000 27.5 -> 23.3, 4096 x 5000
+// 53.8 -> 49.3).
+template <typename R, bool kSelf, bool kLarge>
 __global__ __launch_bounds__(kFwdBlock, sizeof(R) == 8 ? 3 : 1) void k_forward_split(
     FwdJob job, LcInfo lc, GridDev g, const R* __restrict__ T,
     const double* __restrict__ inv_istar, SplitInfo si) {
     const int b = int(blockIdx.x);
     const int n2 = job.npv * si.shares;
-    if (b < n2) {
-        const int ipv = b / si.shares;
-        transit_share<R, kSelf>(job, lc, si, ipv, b - ipv * si.shares, g, T, inv_istar);
+    int before = min(n2, b);                  // transit workgroups before this one
+    bool transit = b < n2;
+    if (kLarge) {
+        const int nt = 8 * si.run_transit, run = nt + 8 * si.run_stream;
+        const int pos = b % run;
+        before = min(n2, b / run * nt + min(pos, nt));
+        transit = pos < nt && before < n2;
+    }
+    if (transit) {
+        const int ipv = before / si.shares;
+        transit_share<R, kSelf>(job, lc, si, ipv, before - ipv * si.shares, g, T, inv_istar);
         return;
     }
-    const int u = b - n2;
+    const int u = b - before;
     const int rg = u / job.ntiles;
     const int r0 = rg * si.rows_per;
     const int r1 = r0 + si.rows_per < job.npv ? r0 + si.rows_per : job.npv;
-    stream_rows<R, kTimesPerThread, kSelf>(job, lc, si, r0, r1, u - rg * job.ntiles);
+    if (kLarge && si.bypass)
+        stream_rows<R, kTimesPerThread, kSelf, true>(job, lc, si, r0, r1, u - rg * job.ntiles);
+    else
+        stream_rows<R, kTimesPerThread, kSelf, false>(job, lc, si, r0, r1, u - rg * job.ntiles);
 }
 
 // The light curves' description in LDS, one light curve per lane: indexed
@@ -901,14 +920,14 @@ static SplitCapacity split_capacity(int32_t precision, bool self) {
     hipError_t e;
     if (precision == RR_FP64)
         e = self ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                       &per_cu, k_forward_split<double, true>, kFwdBlock, 0)
+                       &per_cu, k_forward_split<double, true, false>, kFwdBlock, 0)
                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                       &per_cu, k_forward_split<double, false>, kFwdBlock, 0);
+                       &per_cu, k_forward_split<double, false, false>, kFwdBlock, 0);
     else
         e = self ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                       &per_cu, k_forward_split<float, true>, kFwdBlock, 0)
+                       &per_cu, k_forward_split<float, true, false>, kFwdBlock, 0)
                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                       &per_cu, k_forward_split<float, false>, kFwdBlock, 0);
+                       &per_cu, k_forward_split<float, false, false>, kFwdBlock, 0);
     if (e != hipSuccess || per_cu <= 0) return {0, 0};
     return cache[key] = {per_cu * ncu, ncu};
 }
@@ -985,7 +1004,32 @@ SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision
         sp.shares =
             int32_t(std::min<int64_t>({16, max_sh, std::max<int64_t>(1, n_transit / npv)}));
     }
-    sp.blocks = int64_t(npv) * sp.shares + ntiles * ((npv + sp.rows_per - 1) / sp.rows_per);
+    const int64_t n2 = int64_t(npv) * sp.shares;
+    const int64_t n_stream = ntiles * ((npv + sp.rows_per - 1) / sp.rows_per);
+    if (!sp.self_setup) {
+        // Where the transit workgroups would fill the chip and the streaming
+        // ones wait for them, the two alternate, two eights to three, so that
+        // neither the memory nor the arithmetic idles (us per call, plain order
+        // / 2 : 3; FP64 1024 x 50 000 85 / 79, 4096 x 5000 49 / 45, 8192 x 5000
+        // 80 / 68; float 1024 x 50 000 59.5 / 56, 8192 x 5000 57 / 52); not with
+        // fewer (float 4096 x 5000: 27.5 / 28.5) nor where little streaming is
+        // left to follow the last of them.  Periods divisible by four, the
+        // SIMDs of a CU, put the transits on some of the SIMDs alone: 1 : 1 and
+        // 1 : 3 took 116 and 139 us for the first.
+        if (n2 >= cap && n_stream >= 2 * n2) {
+            sp.run_transit = 2;
+            sp.run_stream = 3;
+        }
+        // An output larger than the last-level cache (256 MB) is stored past
+        // it: no later reader could find it there, and everything else stays
+        // (FP64 1024 x 50 000: 105 -> 85 us, with a matrix-vector product over
+        // the result 226 -> 202; float 2048 x 50 000: 110 -> 81, 224 -> 198).
+        // Smaller outputs are faster that way too, but their readers lose more
+        // (float 1024 x 50 000: 59.5 -> 46, 108 -> 141).
+        const size_t elt = precision == RR_FP64 ? sizeof(double) : sizeof(float);
+        sp.bypass = size_t(npv) * size_t(se->npt) * elt > (size_t(256) << 20);
+    }
+    sp.blocks = n2 + n_stream;
     return sp;
 }
 
@@ -1010,26 +1054,27 @@ hipError_t launch_forward_split(const rr_tables* t, const rr_series* se, const S
     si.buckets = se->buckets;
     si.shares = sp.shares;
     si.rows_per = sp.rows_per;
+    si.run_transit = sp.run_transit;
+    si.run_stream = sp.run_stream;
+    si.bypass = sp.bypass ? 1 : 0;
     si.k_lo = t->grid.k0;
     si.k_hi = t->grid.k1;
     const dim3 grid{unsigned(blocks), 1u, 1u};
     const dim3 block{unsigned(kFwdBlock), 1u, 1u};
     const KernelEvents ev = kernel_events();
-    if (precision == RR_FP64) {
-        if (sp.self_setup)
-            launch_timed(k_forward_split<double, true>, grid, block, 0, s, ev.before, ev.after,
-                         job, se->lc, g, t->T64, t->inv_istar, si);
-        else
-            launch_timed(k_forward_split<double, false>, grid, block, 0, s, ev.before, ev.after,
-                         job, se->lc, g, t->T64, t->inv_istar, si);
-    } else {
-        if (sp.self_setup)
-            launch_timed(k_forward_split<float, true>, grid, block, 0, s, ev.before, ev.after,
-                         job, se->lc, g, t->T32, t->inv_istar, si);
-        else
-            launch_timed(k_forward_split<float, false>, grid, block, 0, s, ev.before, ev.after,
-                         job, se->lc, g, t->T32, t->inv_istar, si);
-    }
+    auto launch = [&](auto kernel, const auto* T) {
+        launch_timed(kernel, grid, block, 0, s, ev.before, ev.after, job, se->lc, g, T,
+                     t->inv_istar, si);
+    };
+    const bool large = !sp.self_setup && (sp.bypass || sp.run_stream > 0);
+    if (precision == RR_FP64)
+        launch(sp.self_setup ? k_forward_split<double, true, false>
+                             : (large ? k_forward_split<double, false, true>
+                                      : k_forward_split<double, false, false>), t->T64);
+    else
+        launch(sp.self_setup ? k_forward_split<float, true, false>
+                             : (large ? k_forward_split<float, false, true>
+                                      : k_forward_split<float, false, false>), t->T32);
     return hipGetLastError();
 }
 

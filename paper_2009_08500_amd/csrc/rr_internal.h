@@ -113,6 +113,8 @@ struct SplitInfo {
     const int32_t* buckets;    // device
     int32_t shares;
     int32_t rows_per;          // rows per streaming workgroup
+    int32_t run_transit, run_stream;   // order of the two kinds, in eights (kLarge)
+    int32_t bypass;            // 1: groups outside every window stored past the caches
     double k_lo, k_hi;         // accepted k range of the rows (the tables')
 };
 
@@ -294,13 +296,14 @@ hipError_t launch_istar_from_profile(rr_tables* t, hipStream_t s);
 // otherwise.
 bool split_preferred(const rr_tables* t, const rr_series* se, int32_t npv, int32_t precision);
 // Shape of a split launch over a registered, indexed series: transit
-// workgroups per row, rows per streaming workgroup, the grid size, and
-// whether the workgroups derive their rows' constants themselves (then no
-// per-row setup precedes the launch).
+// workgroups per row, rows per streaming workgroup, the order of the two
+// kinds, the grid size, whether the workgroups derive their rows' constants
+// themselves (then no per-row setup precedes the launch), and whether the
+// streaming stores pass the caches.
 struct SplitPlan {
-    int32_t shares = 1, rows_per = 1;
+    int32_t shares = 1, rows_per = 1, run_transit = 1, run_stream = 0;
     int64_t blocks = 0;
-    bool self_setup = false;
+    bool self_setup = false, bypass = false;
 };
 SplitPlan plan_forward_split(const rr_series* se, int32_t npv, int32_t precision);
 // The split launch (rr_evaluate_series); pvc (the per-row setup's output)
