@@ -24,7 +24,7 @@
 //               into the wave's own LDS copy of d logL / d ldw (no two waves
 //               share an address, and one wave's LDS additions complete in
 //               program order); the copies are added in wave order and
-//               stored once per workgroup, and k_prof_seg_sum adds a
+//               stored once per workgroup, and k_adjoint_sums adds a
 //               vector's workgroups in order.  Every sum therefore has an
 //               order fixed by the inputs alone: the gradient is bitwise
 //               reproducible.
@@ -32,9 +32,10 @@
 //               a tile of 2048 exposures and evaluating the flagged ones
 //               where they stood), 1024 walkers x 50 000 times x 5: float
 //               132 -> 61 us, FP64 with the profile gradient 414 -> 148 us.
-//   k_adjoint_reduce   per parameter vector, the workgroup partials and the
+//   k_adjoint_sums   per parameter vector, the workgroup partials and the
 //               blocks' sums in a fixed order (lanes, then a butterfly) ->
-//               logL and the gradient row.
+//               logL and the gradient row; the profile gradient's sums per
+//               vector, and its k-rows, in the same launch.
 //   k_table_grad d logL / d T[pb][i][m] from the per-vector d logL / d ldw
 //               through the k-interpolation weights: chunks of vectors in
 //               parallel, each in order, then the chunks in order.
@@ -178,6 +179,22 @@ __device__ inline double flagged_sum(int n, F flag, V val, bool* any = nullptr) 
     if (any) *any = a;
     return s;
 }
+
+// Arguments of the sums after the main kernel (k_adjoint_sums).
+struct AdjointSums {
+    int64_t n_reduce, n_seg;                // workgroups of the first two parts
+    const double* partials;
+    const double* blk_ll;
+    double *logl, *grad;
+    const double *seg_gw, *seg_gi;
+    const int32_t* seg_flag;
+    double *gldw_pv, *gist_pv;
+    const double* pv;
+    const PvConst* pvc;
+    int32_t* kidx;
+    double* kfrac;
+    int32_t npv, nparts, npb, nw, nblk, npar;
+};
 
 // What every row needs before the main kernel, in one launch.  Workgroups
 // [0, nrow_blocks): the per-row constants, one thread per row.  The others:
@@ -555,25 +572,21 @@ __global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) voi
 }
 
 // d logL / d ldw_row and d logL / d I_star per vector: the flagged parts of
-// k_adjoint added in part order.  Thread idx < npv npb ng sums
-// one ldw entry, the next npv npb threads one I_star entry each.
-__global__ void k_prof_seg_sum(const double* __restrict__ seg_gw,
-                               const double* __restrict__ seg_gi,
-                               const int32_t* __restrict__ seg_flag, int32_t npv, int32_t nseg,
-                               int32_t nw, int32_t npb, double* __restrict__ gldw_pv,
-                               double* __restrict__ gist_pv) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t n1 = int64_t(npv) * nw;
+// k_adjoint added in part order.  idx < npv nw sums one ldw entry, the next
+// npv npb one I_star entry each.
+__device__ inline void prof_seg_sum(int64_t idx, const AdjointSums& a) {
+    const int64_t n1 = int64_t(a.npv) * a.nw;
+    const int nseg = a.nparts;
     if (idx < n1) {
-        const int64_t ipv = idx / nw, e = idx - ipv * nw;
-        gldw_pv[idx] = flagged_sum(
-            nseg, [&](int sg) { return seg_flag[ipv * nseg + sg] != 0; },
-            [&](int sg) { return seg_gw[(ipv * nseg + sg) * nw + e]; });
-    } else if (idx < n1 + int64_t(npv) * npb) {
-        const int64_t j = idx - n1, ipv = j / npb, pb = j - ipv * npb;
-        gist_pv[j] = flagged_sum(
-            nseg, [&](int sg) { return seg_flag[ipv * nseg + sg] != 0; },
-            [&](int sg) { return seg_gi[(ipv * nseg + sg) * npb + pb]; });
+        const int64_t ipv = idx / a.nw, e = idx - ipv * a.nw;
+        a.gldw_pv[idx] = flagged_sum(
+            nseg, [&](int sg) { return a.seg_flag[ipv * nseg + sg] != 0; },
+            [&](int sg) { return a.seg_gw[(ipv * nseg + sg) * a.nw + e]; });
+    } else if (idx < n1 + int64_t(a.npv) * a.npb) {
+        const int64_t j = idx - n1, ipv = j / a.npb, pb = j - ipv * a.npb;
+        a.gist_pv[j] = flagged_sum(
+            nseg, [&](int sg) { return a.seg_flag[ipv * nseg + sg] != 0; },
+            [&](int sg) { return a.seg_gi[(ipv * nseg + sg) * a.npb + pb]; });
     }
 }
 
@@ -585,25 +598,22 @@ __global__ void k_fill(double* __restrict__ p, int64_t n) {
 // One wave per (row, quantity): lane l sums the partials of parts l, l + 64,
 // ... in order, then a fixed butterfly across the lanes; logL adds the sum
 // over every exposure with F = 1, its time blocks summed the same way.
-__global__ void k_adjoint_reduce(const double* __restrict__ partials, int32_t npv,
-                                 int32_t nparts, int32_t npb, int32_t nblk,
-                                 const double* __restrict__ blk_ll, double* __restrict__ logl,
-                                 double* __restrict__ grad) {
-    const int nq = kNq + npb;
-    const int64_t wv = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+__device__ inline void adjoint_reduce(int64_t wv, const AdjointSums& a) {
+    const int nq = kNq + a.npb;
     const int lane = threadIdx.x & 63;
-    if (wv >= int64_t(npv) * nq) return;                 // whole waves leave together
+    if (wv >= int64_t(a.npv) * nq) return;               // whole waves leave together
     const int ipv = int(wv / nq), q = int(wv - int64_t(ipv) * nq);
     double s = 0.0;
-    for (int c = lane; c < nparts; c += 64) s += partials[(int64_t(ipv) * nparts + c) * nq + q];
-    if (q == 0 && logl)
-        for (int b = lane; b < nblk; b += 64) s += blk_ll[b];
+    for (int c = lane; c < a.nparts; c += 64)
+        s += a.partials[(int64_t(ipv) * a.nparts + c) * nq + q];
+    if (q == 0 && a.logl)
+        for (int b = lane; b < a.nblk; b += 64) s += a.blk_ll[b];
     s = wave_sum(s);
     if (lane != 0) return;
     if (q == 0) {
-        if (logl) logl[ipv] = s;
-    } else if (grad) {
-        grad[int64_t(ipv) * (6 + npb) + (q - 1)] = s;
+        if (a.logl) a.logl[ipv] = s;
+    } else if (a.grad) {
+        a.grad[int64_t(ipv) * (6 + a.npb) + (q - 1)] = s;
     }
 }
 
@@ -611,22 +621,36 @@ __global__ void k_adjoint_reduce(const double* __restrict__ partials, int32_t np
 // gradient: kidx = ik (kNoRow for an invalid row, so that neither ik nor
 // ik + 1 matches any k-row), kfrac = ak.
 constexpr int kNoRow = -2;
-__global__ void k_row_kidx(const double* __restrict__ pv, int32_t npv, int32_t npar,
-                           const PvConst* __restrict__ pvc, GridDev g,
-                           int32_t* __restrict__ kidx, double* __restrict__ kfrac) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= int64_t(npv) * g.npb) return;
-    const int ipv = int(idx / g.npb), pb = int(idx - int64_t(ipv) * g.npb);
-    if (!(pvc[ipv].flags & kValid)) {
-        kidx[idx] = kNoRow;
-        kfrac[idx] = 0.0;
+__device__ inline void row_kidx(int64_t idx, const AdjointSums& a, const GridDev& g) {
+    if (idx >= int64_t(a.npv) * a.npb) return;
+    const int ipv = int(idx / a.npb), pb = int(idx - int64_t(ipv) * a.npb);
+    if (!(a.pvc[ipv].flags & kValid)) {
+        a.kidx[idx] = kNoRow;
+        a.kfrac[idx] = 0.0;
         return;
     }
-    const double u = (pv[int64_t(ipv) * npar + 6 + pb] - g.k0) / g.dk;
+    const double u = (a.pv[int64_t(ipv) * a.npar + 6 + pb] - g.k0) / g.dk;
     int ik = int(floor(u));
     ik = ik < 0 ? 0 : (ik > g.nk - 2 ? g.nk - 2 : ik);
-    kidx[idx] = ik;
-    kfrac[idx] = u - ik;
+    a.kidx[idx] = ik;
+    a.kfrac[idx] = u - ik;
+}
+
+// The sums that follow k_adjoint, in one launch (each costs about 5 us of
+// launch and memory latency by itself, whatever it sums): workgroups
+// [0, n_reduce) adjoint_reduce, the next n_seg prof_seg_sum, the rest row_kidx.
+__global__ void k_adjoint_sums(AdjointSums a, GridDev g) {
+    int64_t b = blockIdx.x;
+    if (b < a.n_reduce) {
+        adjoint_reduce((b * blockDim.x + threadIdx.x) >> 6, a);
+        return;
+    }
+    b -= a.n_reduce;
+    if (b < a.n_seg) {
+        prof_seg_sum(b * blockDim.x + threadIdx.x, a);
+        return;
+    }
+    row_kidx((b - a.n_seg) * blockDim.x + threadIdx.x, a, g);
 }
 
 // dlogL/dT[pb][i][m] = sum over rows of [(ik == i)(1 - ak) + (ik + 1 == i) ak]
@@ -701,7 +725,7 @@ __global__ void k_table_grad_sum(const double* __restrict__ part,
 
 // dlogL/dldp[pb][j] = sum_{i,m} W[i][j][m] dlogL/dT[pb][i][m], in two fixed-
 // order stages: workgroup (c, j, pb) sums the k-rows of chunk c with a
-// fixed-shape tree, then k_ldp_sum adds the chunks in order.
+// fixed-shape tree, then k_prof_grad adds the chunks in order.
 constexpr int kLdpChunks = 16;
 __global__ void k_ldp_grad(const double* __restrict__ W, const double* __restrict__ GT,
                            const int32_t* __restrict__ rowflag, GridDev g,
@@ -727,33 +751,6 @@ __global__ void k_ldp_grad(const double* __restrict__ W, const double* __restric
     if (threadIdx.x == 0) part_out[(int64_t(pb) * g.nz + j) * kLdpChunks + c] = part[0];
 }
 
-__global__ void k_ldp_sum(const double* __restrict__ part, int32_t n, double* __restrict__ gldp) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n) return;
-    double s = 0.0;
-    for (int c = 0; c < kLdpChunks; ++c) s += part[int64_t(idx) * kLdpChunks + c];
-    gldp[idx] = s;
-}
-
-// Sum over valid rows of dlogL/dI_star[pb], one workgroup per passband,
-// fixed-shape tree.
-__global__ void k_gist_sum(const double* __restrict__ gist_pv, int32_t npv,
-                           const PvConst* __restrict__ pvc, int32_t npb,
-                           double* __restrict__ gist) {
-    __shared__ double part[kBlock];
-    const int pb = blockIdx.x;
-    double s = 0.0;
-    for (int ipv = threadIdx.x; ipv < npv; ipv += kBlock)
-        if (pvc[ipv].flags & kValid) s += gist_pv[int64_t(ipv) * npb + pb];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) gist[pb] = part[0];
-}
-
 // Profile gradient: chain dlogL/dldp (profile at the bin means, linear in
 // the samples with the weights of the piecewise-linear interpolant) and
 // dlogL/dI_star (I_star linear in the samples, Eq. 2 / Eq. 4) back to the
@@ -764,17 +761,38 @@ __global__ void k_gist_sum(const double* __restrict__ gist_pv, int32_t npv,
 // them) and dlogL/dldp[pb][j]; then each thread adds its sample's weights
 // times dlogL/dldp over the chunk's bins in order (only the run of bins that
 // interpolate from its sample).
+//   kShared (one profile for all rows): dlogL/dldp is the sum of k_ldp_grad's
+// chunks in order and dlogL/dI_star the sum over the valid rows, in a fixed
+// tree that every workgroup of a passband repeats, which costs less than the
+// two launches it replaces; grad_istar, if given, gets the latter.
 constexpr int kJChunk = 1024;
 constexpr int kMuLds = 1024;
-__global__ void k_prof_grad(const double* __restrict__ gldp, const double* __restrict__ gist,
-                            const double* __restrict__ mu_s, int32_t nmu,
-                            const double* __restrict__ zm, int32_t nz, int32_t npb,
-                            int32_t istar_fixed, double* __restrict__ out) {
+template <bool kShared>
+__global__ __launch_bounds__(kBlock) void k_prof_grad(
+    const double* __restrict__ gldp, const double* __restrict__ gist_pv, int32_t npv,
+    const PvConst* __restrict__ pvc, const double* __restrict__ mu_s, int32_t nmu,
+    const double* __restrict__ zm, int32_t nz, int32_t npb, int32_t istar_fixed,
+    double* __restrict__ grad_istar, double* __restrict__ out) {
     __shared__ int seg_lo[kJChunk];
     __shared__ double seg_tau[kJChunk];
     __shared__ double gl[kJChunk];
     __shared__ double mu_l[kMuLds];
     const int pb = blockIdx.y;
+    double gist = kShared ? 0.0 : gist_pv[pb];
+    if (kShared) {
+        __shared__ double part[kBlock];
+        for (int ipv = threadIdx.x; ipv < npv; ipv += kBlock)
+            if (pvc[ipv].flags & kValid) gist += gist_pv[int64_t(ipv) * npb + pb];
+        part[threadIdx.x] = gist;
+        __syncthreads();
+        for (int w = kBlock / 2; w > 0; w >>= 1) {
+            if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+            __syncthreads();
+        }
+        gist = part[0];
+        if (grad_istar && blockIdx.x == 0 && threadIdx.x == 0) grad_istar[pb] = gist;
+        if (!out) return;
+    }
     const int s = int(blockIdx.x) * kBlock + int(threadIdx.x);
     const bool staged = nmu <= kMuLds;
     if (staged)
@@ -804,7 +822,11 @@ __global__ void k_prof_grad(const double* __restrict__ gldp, const double* __res
             }
             seg_lo[jj] = lo;
             seg_tau[jj] = tau;
-            gl[jj] = gldp[int64_t(pb) * nz + j0 + jj];
+            const int64_t j = int64_t(pb) * nz + j0 + jj;
+            double sum = kShared ? 0.0 : gldp[j];
+            if (kShared)
+                for (int c = 0; c < kLdpChunks; ++c) sum += gldp[j * kLdpChunks + c];
+            gl[jj] = sum;
         }
         __syncthreads();
         if (s < nmu) {
@@ -849,7 +871,7 @@ __global__ void k_prof_grad(const double* __restrict__ gldp, const double* __res
     if (s == nmu - 1) qs += 0.5 * (1.0 - ms[nmu - 1] * ms[nmu - 1]);
     qs *= 2.0 * Num<double>::pi;
     // a normaliser set by the caller does not depend on the samples
-    out[int64_t(pb) * nmu + s] = istar_fixed ? acc : acc + qs * gist[pb];
+    out[int64_t(pb) * nmu + s] = istar_fixed ? acc : acc + qs * gist;
 }
 
 inline unsigned nblocks(int64_t n) { return unsigned((n + kBlock - 1) / kBlock); }
@@ -938,15 +960,18 @@ hipError_t launch_adjoint(const AdjointArgs& A, size_t lds, int32_t precision, h
     else launch_adjoint_r<float>(A, lds, s, ev);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (A.want_prof && A.nparts > 1) {
-        const int32_t nw = A.g.npb * A.g.ng;
-        hipLaunchKernelGGL(k_prof_seg_sum, dim3(nblocks(int64_t(A.npv) * (nw + A.g.npb))),
-                           dim3(kBlock), 0, s, A.seg_gw, A.seg_gi, A.seg_flag, A.npv, A.nparts,
-                           nw, A.g.npb, A.gldw_pv, A.gist_pv);
-    }
-    hipLaunchKernelGGL(k_adjoint_reduce, dim3(nblocks(int64_t(A.npv) * (kNq + A.g.npb) * 64)),
-                       dim3(kBlock), 0, s, A.partials, A.npv, A.nparts, A.g.npb, A.nblk,
-                       A.blk_ll, A.logl, A.grad);
+    AdjointSums u = {};
+    u.npv = A.npv; u.nparts = A.nparts; u.npb = A.g.npb; u.nw = A.g.npb * A.g.ng;
+    u.nblk = A.nblk; u.npar = A.npar;
+    u.partials = A.partials; u.blk_ll = A.blk_ll; u.logl = A.logl; u.grad = A.grad;
+    u.seg_gw = A.seg_gw; u.seg_gi = A.seg_gi; u.seg_flag = A.seg_flag;
+    u.gldw_pv = A.gldw_pv; u.gist_pv = A.gist_pv;
+    u.pv = A.pv; u.pvc = A.pvc; u.kidx = A.kidx; u.kfrac = A.kfrac;
+    u.n_reduce = nblocks(int64_t(A.npv) * (kNq + A.g.npb) * 64);
+    u.n_seg = A.want_prof && A.nparts > 1 ? nblocks(int64_t(A.npv) * (u.nw + A.g.npb)) : 0;
+    const int64_t n_kidx = A.kidx ? nblocks(int64_t(A.npv) * A.g.npb) : 0;
+    hipLaunchKernelGGL(k_adjoint_sums, dim3(unsigned(u.n_reduce + u.n_seg + n_kidx)),
+                       dim3(kBlock), 0, s, u, A.g);
     return hipGetLastError();
 }
 
@@ -1121,10 +1146,9 @@ hipError_t launch_pv_prof_grad(const rr_tables* t, const AdjointArgs& A, const P
     // profile: its own dlogL/dldp and dlogL/dI_star
     for (int64_t r0 = 0; r0 < nr; r0 += 65535) {
         const int32_t n = int32_t(std::min<int64_t>(65535, nr - r0));
-        hipLaunchKernelGGL(k_prof_grad, dim3(nblocks(t->nmu), unsigned(n)), dim3(kBlock), 0, s,
-                           gldp + r0 * t->nz, A.gist_pv + r0, t->mu_s, t->nmu, t->zm, t->nz, n,
-                           0,
-                           out + r0 * t->nmu);
+        hipLaunchKernelGGL(k_prof_grad<false>, dim3(nblocks(t->nmu), unsigned(n)), dim3(kBlock),
+                           0, s, gldp + r0 * t->nz, A.gist_pv + r0, 0, A.pvc, t->mu_s, t->nmu,
+                           t->zm, t->nz, n, 0, nullptr, out + r0 * t->nmu);
     }
     return hipGetLastError();
 }
@@ -1132,14 +1156,11 @@ hipError_t launch_pv_prof_grad(const rr_tables* t, const AdjointArgs& A, const P
 hipError_t launch_profile_grad(const rr_tables* t, const AdjointArgs& A,
                                const ProfGradScratch& w, double* out, hipStream_t s) {
     const GridDev g = A.g;
-    const int64_t nrk = int64_t(A.npv) * g.npb;
-    hipLaunchKernelGGL(k_row_kidx, dim3(nblocks(nrk)), dim3(kBlock), 0, s, A.pv, A.npv, A.npar,
-                       A.pvc, g, w.kidx, w.kfrac);
     const int32_t rpc = (A.npv + w.nchunks - 1) / w.nchunks;
     hipLaunchKernelGGL(k_table_grad,
                        dim3(unsigned((g.ng + kBlock - 1) / kBlock), unsigned(g.nk),
                             unsigned(w.nchunks * g.npb)),
-                       dim3(kBlock), 0, s, A.gldw_pv, w.kidx, w.kfrac, A.npv, rpc, g,
+                       dim3(kBlock), 0, s, A.gldw_pv, A.kidx, A.kfrac, A.npv, rpc, g,
                        w.gt_part, w.gt_flags);
     hipLaunchKernelGGL(k_table_grad_sum, dim3(nblocks(int64_t(g.npb) * g.nk * g.ng)),
                        dim3(kBlock), 0, s, w.gt_part, w.gt_flags, w.nchunks, g, w.GT,
@@ -1148,21 +1169,9 @@ hipError_t launch_profile_grad(const rr_tables* t, const AdjointArgs& A,
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_ldp_grad, dim3(unsigned(kLdpChunks), unsigned(g.nz), unsigned(g.npb)),
                        dim3(kBlock), 0, s, t->W, w.GT, w.gt_rowflag, g, w.ldp_part);
-    hipLaunchKernelGGL(k_ldp_sum, dim3(nblocks(int64_t(g.npb) * g.nz)), dim3(kBlock), 0, s,
-                       w.ldp_part, g.npb * g.nz, w.gldp);
-    hipLaunchKernelGGL(k_gist_sum, dim3(unsigned(g.npb)), dim3(kBlock), 0, s, A.gist_pv, A.npv,
-                       A.pvc, g.npb, w.gist);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (w.grad_istar) {
-        e = hipMemcpyAsync(w.grad_istar, w.gist, sizeof(double) * g.npb,
-                           hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return e;
-    }
-    if (out)
-        hipLaunchKernelGGL(k_prof_grad, dim3(nblocks(t->nmu), unsigned(g.npb)), dim3(kBlock), 0,
-                           s, w.gldp, w.gist, t->mu_s, t->nmu, t->zm, t->nz, g.npb,
-                           w.istar_fixed, out);
+    hipLaunchKernelGGL(k_prof_grad<true>, dim3(out ? nblocks(t->nmu) : 1, unsigned(g.npb)),
+                       dim3(kBlock), 0, s, w.ldp_part, A.gist_pv, A.npv, A.pvc, t->mu_s, t->nmu,
+                       t->zm, t->nz, g.npb, w.istar_fixed, w.grad_istar, out);
     return hipGetLastError();
 }
 

@@ -867,11 +867,9 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
     const size_t o_rows = own_rows ? take(elt * size_t(nr) * 2 * g.ng) : 0;
     const size_t o_gldpr = per_row && prof ? take(sizeof(double) * size_t(nr) * t->nz) : 0;
     const size_t o_gt = shared_prof ? take(sizeof(double) * size_t(t->npb) * g.nk * g.ng) : 0;
-    const size_t o_gldp = shared_prof ? take(sizeof(double) * size_t(t->npb) * t->nz) : 0;
     const size_t o_ldpp = shared_prof ? take(sizeof(double) * size_t(t->npb) * t->nz * 16) : 0;
     const size_t o_kidx = shared_prof ? take(sizeof(int32_t) * size_t(npv) * t->npb) : 0;
     const size_t o_kfrac = shared_prof ? take(sizeof(double) * size_t(npv) * t->npb) : 0;
-    const size_t o_gist_sum = shared_prof ? take(sizeof(double) * size_t(t->npb)) : 0;
     // table-gradient row chunks: up to 32 rows each, at most 64 chunks and
     // 256 MiB of partial tables
     const size_t table_bytes = sizeof(double) * size_t(t->npb) * g.nk * g.ng;
@@ -912,6 +910,8 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
     A.seg_gi = segs ? reinterpret_cast<double*>(base + o_sgi) : nullptr;
     A.seg_flag = segs ? reinterpret_cast<int32_t*>(base + o_sfl) : nullptr;
     A.logl = logl_d; A.grad = grad_d;
+    A.kidx = shared_prof ? reinterpret_cast<int32_t*>(base + o_kidx) : nullptr;
+    A.kfrac = shared_prof ? reinterpret_cast<double*>(base + o_kfrac) : nullptr;
     const size_t lds = adjoint_plan_lds(precision, t->lds_max, &A);
     e = launch_adjoint_prep(A, precision, t->grid.k0, t->grid.k1, sp ? k_small : 0.0, stream);
     if (e == hipSuccess && sp)
@@ -931,16 +931,12 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
                                 precision == RR_MIXED);
     if (e == hipSuccess && shared_prof) {
         ProfGradScratch w;
-        w.kidx = reinterpret_cast<int32_t*>(base + o_kidx);
-        w.kfrac = reinterpret_cast<double*>(base + o_kfrac);
         w.nchunks = nchunks;
         w.gt_part = reinterpret_cast<double*>(base + o_gtp);
         w.gt_flags = reinterpret_cast<int32_t*>(base + o_gtf);
         w.gt_rowflag = reinterpret_cast<int32_t*>(base + o_gtr);
         w.GT = reinterpret_cast<double*>(base + o_gt);
         w.ldp_part = reinterpret_cast<double*>(base + o_ldpp);
-        w.gldp = reinterpret_cast<double*>(base + o_gldp);
-        w.gist = reinterpret_cast<double*>(base + o_gist_sum);
         w.istar_fixed = t->istar_fixed ? 1 : 0;
         w.grad_istar = grad_istar_d;
         e = launch_profile_grad(t, A, w, grad_prof_d, stream);

@@ -157,6 +157,10 @@ struct AdjointArgs {
     double* seg_gi;           // [npv][nparts][npb]
     int32_t* seg_flag;        // [npv][nparts]
     double* logl;             // [npv] or null
+    // shared profile: each (row, passband)'s k-row and lerp weight for the table
+    // gradient, [npv][npb], or null
+    int32_t* kidx;
+    double* kfrac;
     double* grad;             // [npv][npar] or null
 };
 
@@ -262,16 +266,12 @@ hipError_t launch_adjoint_prep(const AdjointArgs& a, int32_t precision, double k
 hipError_t launch_adjoint(const AdjointArgs& a, size_t lds, int32_t precision, hipStream_t s);
 // Temporaries of the profile gradient.
 struct ProfGradScratch {
-    int32_t* kidx;        // [npv][npb]
-    double* kfrac;        // [npv][npb]
     int32_t nchunks;      // row chunks of the table gradient
     double* gt_part;      // [nchunks][npb][nk][ng]
     int32_t* gt_flags;    // [nchunks][npb][nk]
     int32_t* gt_rowflag;  // [npb][nk]: k-row touched by any chunk
     double* GT;           // [npb][nk][ng]
     double* ldp_part;     // [npb][nz][16]
-    double* gldp;         // [npb][nz]
-    double* gist;         // [npb]
     int32_t istar_fixed;  // 1: I_star does not depend on the samples (rr_set_istar)
     double* grad_istar;   // [npb] output (d logL / d I_star) or null
 };
