@@ -667,7 +667,7 @@ RR_API int rr_evaluate_direct(const rr_tables* t, const double* times_d,
     // any k in (0, 1]: the smallest positive double as the lower bound
     e = launch_pv_setup_k(pv_d, npv, npar, 4.9406564584124654e-324, 1.0, pvc, precision,
                           stream);
-    if (e == hipSuccess) e = launch_direct_rows(t, pv_d, npv, npar, precision, rows, stream);
+    if (e == hipSuccess) e = launch_direct_rows(t, pv_d, pvc, npv, npar, precision, rows, stream);
     if (e == hipSuccess)
         e = launch_forward(t, times_d, lcids_d, npt, lc, pv_d, npv, npar, pvc, precision,
                            out_d, stream, rows, nullptr, 1);

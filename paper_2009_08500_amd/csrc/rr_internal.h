@@ -325,8 +325,9 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
                           int32_t variant = kDefaultFwdVariant);
 // Direct model (rr_evaluate_direct): each (vector, passband) row's
 // LD-weighted vector for its own k, rows [npv][npb][2][ng] by precision.
-hipError_t launch_direct_rows(const rr_tables* t, const double* pv, int32_t npv, int32_t npar,
-                              int32_t precision, void* rows, hipStream_t s);
+hipError_t launch_direct_rows(const rr_tables* t, const double* pv, const PvConst* pvc,
+                              int32_t npv, int32_t npar, int32_t precision, void* rows,
+                              hipStream_t s);
 // Small-planet approximation (rr_evaluate_small_planet): rows
 // [npv][npb][2][ng] by precision; a row whose k is below k_small holds the
 // profile at the planet's centre for each g node, any other the tables' two

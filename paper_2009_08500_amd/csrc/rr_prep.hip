@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kBlock) void k_pv_prep(const double* __restrict__ m
     const double* row = pv + ipv * npar;
     if (threadIdx.x == kBlock - 1 && pvc && pb == 0)
         pvc[ipv] = make_pv_const<kF32>(row, g.npb, g.k0, k1);
-    if (threadIdx.x == kBlock - 65) ord.mlo[r] = lowest_node(row, row[6 + pb], g);
+    if (threadIdx.x == kBlock - 65) ord.mlo[r] = lowest_node(row, sin(row[5]), row[6 + pb], g);
     for (int j = threadIdx.x; j < nz; j += kBlock) ldp[r * nz + j] = profile_at_bin(mu_s, f, nmu, zm[j]);
     istar_block(mu_s, f, nmu, istar + r, inv_istar + r);
 }
@@ -567,8 +567,11 @@ __global__ __launch_bounds__(kBlock, 3) void k_pv_tables(const WT* __restrict__ 
 // stationary in h, so the cancellation in R - x near a contact does not reach
 // it.  Workgroup: 64 nodes of one row, one per lane, whose edges its waves
 // share in turn (with one wave per 64 nodes the limb's nodes, which cross up
-// to 120 edges, ran on alone: 86 us), the limb's nodes first.
-// 512 rows, default grid, FP64: 182 us with every edge evaluated, 59 now.
+// to 120 edges, ran on alone: 86 us), the limb's nodes first; nodes below the
+// row's lowest_node are left out.
+// 512 rows, default grid, FP64: 182 us with every edge evaluated, 59 without
+// those that need not be, 55 without the nodes no exposure reads either (a third
+// of them, but the cheap ones near the centre).
 constexpr int kDirectWaves = 4;            // 66 / 59 / 63 us with 2 / 4 / 8
 // sqrt of a normal x > 0 from the hardware's reciprocal square root and two
 // refinements: within an ulp or two, without the library's scaling and its
@@ -584,7 +587,8 @@ __device__ inline double sqrt_nr(double x) {
 template <typename R>
 __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
     const double* __restrict__ ze, const double* __restrict__ ldp, const double* __restrict__ pv,
-    int32_t npar, int64_t nr, int32_t nz, GridDev g, R* __restrict__ out) {
+    const PvConst* __restrict__ pvc, int32_t npar, int64_t nr, int32_t nz, GridDev g,
+    R* __restrict__ out) {
     extern __shared__ double direct_lds[];
     double* edge = direct_lds;                     // edges 1 .. nz - 1, at j - 1
     double* dl = direct_lds + (nz - 1);            // l_j - l_{j-1}, at j - 1
@@ -601,9 +605,13 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
         edge[j - 1] = ze[j];
         dl[j - 1] = l[j] - l[j - 1];
     }
-    __syncthreads();
-    const int m = mb * 64 + lane;
     const double k = pv[ipv * npar + 6 + pb];
+    __shared__ int low;
+    if (threadIdx.x == 64 * kDirectWaves - 1)
+        low = pvc[ipv].flags & kValid ? lowest_node(pv + ipv * npar, pvc[ipv].sinw, k, g) : 0;
+    __syncthreads();
+    if (mb * 64 + 63 < low) return;                // no exposure reads these nodes
+    const int m = mb * 64 + lane;
     const bool valid = k > 0.0 && k <= 1.0;        // uniform
     using N = Num<double>;
     const double c = (double(m) / double(g.ng - 1)) * (1.0 + k);
@@ -711,8 +719,9 @@ __global__ __launch_bounds__(kBlock) void k_small_planet_rows(
     o[g.ng + m] = v;
 }
 
-hipError_t launch_direct_rows(const rr_tables* t, const double* pv, int32_t npv, int32_t npar,
-                              int32_t precision, void* rows, hipStream_t s) {
+hipError_t launch_direct_rows(const rr_tables* t, const double* pv, const PvConst* pvc,
+                              int32_t npv, int32_t npar, int32_t precision, void* rows,
+                              hipStream_t s) {
     const GridDev g = grid_dev(t);
     const int64_t nr = int64_t(npv) * t->npb;
     const int64_t blocks = nr * ((g.ng + 63) / 64);
@@ -721,11 +730,11 @@ hipError_t launch_direct_rows(const rr_tables* t, const double* pv, int32_t npv,
     const size_t lds = sizeof(double) * std::max<size_t>(2 * size_t(t->nz - 1),
                                                          64 * (kDirectWaves - 1));
     if (precision == RR_FP64)
-        hipLaunchKernelGGL(k_direct_rows<double>, grid, dim3(64 * kDirectWaves), lds, s, t->ze, t->ldp, pv,
-                           npar, nr, t->nz, g, static_cast<double*>(rows));
+        hipLaunchKernelGGL(k_direct_rows<double>, grid, dim3(64 * kDirectWaves), lds, s, t->ze,
+                           t->ldp, pv, pvc, npar, nr, t->nz, g, static_cast<double*>(rows));
     else
-        hipLaunchKernelGGL(k_direct_rows<float>, grid, dim3(64 * kDirectWaves), lds, s, t->ze, t->ldp, pv,
-                           npar, nr, t->nz, g, static_cast<float*>(rows));
+        hipLaunchKernelGGL(k_direct_rows<float>, grid, dim3(64 * kDirectWaves), lds, s, t->ze,
+                           t->ldp, pv, pvc, npar, nr, t->nz, g, static_cast<float*>(rows));
     return hipGetLastError();
 }
 
