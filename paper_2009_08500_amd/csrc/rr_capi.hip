@@ -664,10 +664,7 @@ RR_API int rr_evaluate_direct(const rr_tables* t, const double* times_d,
     char* base = static_cast<char*>(ws);
     PvConst* pvc = reinterpret_cast<PvConst*>(base + o_pvc);
     void* rows = base + o_rows;
-    // any k in (0, 1]: the smallest positive double as the lower bound
-    e = launch_pv_setup_k(pv_d, npv, npar, 4.9406564584124654e-324, 1.0, pvc, precision,
-                          stream);
-    if (e == hipSuccess) e = launch_direct_rows(t, pv_d, pvc, npv, npar, precision, rows, stream);
+    e = launch_direct_rows(t, pv_d, pvc, npv, npar, precision, rows, stream);
     if (e == hipSuccess)
         e = launch_forward(t, times_d, lcids_d, npt, lc, pv_d, npv, npar, pvc, precision,
                            out_d, stream, rows, nullptr, 1);
@@ -704,10 +701,7 @@ RR_API int rr_evaluate_small_planet(const rr_tables* t, const double* times_d,
     char* base = static_cast<char*>(ws);
     PvConst* pvc = reinterpret_cast<PvConst*>(base + o_pvc);
     void* rows = base + o_rows;
-    e = launch_pv_setup_k(pv_d, npv, npar, t->grid.k0, t->grid.k1, pvc, precision, stream,
-                          k_small);
-    if (e == hipSuccess)
-        e = launch_small_planet_rows(t, pv_d, npv, npar, k_small, precision, rows, stream);
+    e = launch_small_planet_rows(t, pv_d, npv, npar, k_small, precision, pvc, rows, stream);
     if (e == hipSuccess)
         e = launch_forward(t, times_d, lcids_d, npt, lc, pv_d, npv, npar, pvc, precision,
                            out_d, stream, rows, nullptr, 1);

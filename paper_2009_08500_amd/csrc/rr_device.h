@@ -543,10 +543,9 @@ __device__ inline int64_t flat_block() {
 // row leave the nodes below it out (a third of them for impact parameters
 // uniform in [0, 0.9]).  The margins cover the rounding of z in float (a few
 // 1e-7 of a) and the node below a z on a node; 0 for a row that is not valid.
-__device__ inline int lowest_node(const double* __restrict__ row, double sinw, double k,
-                                  const GridDev& g) {
-    const double a = row[2], b = row[3], e = row[4];
-    const double z = b * (1.0 + e * sinw) / (1.0 + e) * (1.0 - 1e-5) - 4e-6 * a;
+__device__ inline int lowest_node(const double* __restrict__ row, double k, const GridDev& g) {
+    const double a = row[2], b = row[3], e = row[4], w = row[5];
+    const double z = b * (1.0 + e * sin(w)) / (1.0 + e) * (1.0 - 1e-5) - 4e-6 * a;
     const double v = z / (1.0 + k) * g.gscale - 2.0;
     if (!(v > 0.0) || !(e >= 0.0) || !(e < 1.0) || !(k > 0.0)) return 0;
     return v < double(g.ng - 1) ? int(v) : g.ng - 1;

@@ -46,11 +46,10 @@ static_assert(kTimesPerThread % 4 == 0 && kTimesPerThread <= 32,
 
 template <bool kF32>
 __global__ void k_pv_setup(const double* __restrict__ pv, int32_t npv,
-                           int32_t npar, double k0, double k1, double k_small,
-                           PvConst* __restrict__ out) {
+                           int32_t npar, double k0, double k1, PvConst* __restrict__ out) {
     const int ipv = blockIdx.x * blockDim.x + threadIdx.x;
     if (ipv >= npv) return;
-    out[ipv] = make_pv_const<kF32>(pv + int64_t(ipv) * npar, npar - 6, k0, k1, k_small);
+    out[ipv] = make_pv_const<kF32>(pv + int64_t(ipv) * npar, npar - 6, k0, k1);
 }
 
 // Per-row, per-passband constants of pass 2: the two k-rows of T that
@@ -823,18 +822,12 @@ inline unsigned nblocks(int64_t n) { return unsigned((n + kBlock - 1) / kBlock);
 
 hipError_t launch_pv_setup(const rr_tables* t, const double* pv, int32_t npv,
                            int32_t npar, PvConst* pvc, int32_t precision, hipStream_t s) {
-    return launch_pv_setup_k(pv, npv, npar, t->grid.k0, t->grid.k1, pvc, precision, s);
-}
-
-hipError_t launch_pv_setup_k(const double* pv, int32_t npv, int32_t npar, double k_lo,
-                             double k_hi, PvConst* pvc, int32_t precision, hipStream_t s,
-                             double k_small) {
     if (precision == RR_FP64)
         hipLaunchKernelGGL(k_pv_setup<false>, dim3(nblocks(npv)), dim3(kBlock), 0, s, pv, npv,
-                           npar, k_lo, k_hi, k_small, pvc);
+                           npar, t->grid.k0, t->grid.k1, pvc);
     else
         hipLaunchKernelGGL(k_pv_setup<true>, dim3(nblocks(npv)), dim3(kBlock), 0, s, pv, npv,
-                           npar, k_lo, k_hi, k_small, pvc);
+                           npar, t->grid.k0, t->grid.k1, pvc);
     return hipGetLastError();
 }
 

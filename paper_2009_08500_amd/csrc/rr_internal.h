@@ -242,14 +242,10 @@ rr::GridDev grid_dev(const rr_tables* t);
 // Kernel launchers (rr_prep.hip, rr_forward.hip).
 hipError_t launch_prepare_grid_weights(rr_tables* t, hipStream_t s);
 hipError_t launch_prepare_profile(rr_tables* t, hipStream_t s);
-// Per-row constants for the forward paths of `precision`; k must lie in
-// [k_lo, k_hi] (the tables' k range by default; the direct model takes
-// (0, 1]), or in (0, k_small) for small-planet rows.
+// Per-row constants for the forward paths of `precision`; k must lie in the
+// tables' k range.
 hipError_t launch_pv_setup(const rr_tables* t, const double* pv, int32_t npv,
                            int32_t npar, PvConst* pvc, int32_t precision, hipStream_t s);
-hipError_t launch_pv_setup_k(const double* pv, int32_t npv, int32_t npar, double k_lo,
-                             double k_hi, PvConst* pvc, int32_t precision, hipStream_t s,
-                             double k_small = 0.0);
 // The dynamic LDS one log-likelihood workgroup cannot do without: the
 // k-interpolated LD vectors and their k-derivatives, plus (prof) each wave's
 // copy of d logL / d ldw and d logL / d I_star.
@@ -324,17 +320,19 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
                           const double* inv_istar_pv = nullptr, int32_t ldw_exact_k = 0,
                           int32_t variant = kDefaultFwdVariant);
 // Direct model (rr_evaluate_direct): each (vector, passband) row's
-// LD-weighted vector for its own k, rows [npv][npb][2][ng] by precision.
-hipError_t launch_direct_rows(const rr_tables* t, const double* pv, const PvConst* pvc,
+// LD-weighted vector for its own k, rows [npv][npb][2][ng] by precision, and
+// the rows' constants pvc.
+hipError_t launch_direct_rows(const rr_tables* t, const double* pv, PvConst* pvc,
                               int32_t npv, int32_t npar, int32_t precision, void* rows,
                               hipStream_t s);
 // Small-planet approximation (rr_evaluate_small_planet): rows
 // [npv][npb][2][ng] by precision; a row whose k is below k_small holds the
 // profile at the planet's centre for each g node, any other the tables' two
-// k-rows already interpolated at its k (read with zero k-weight).
+// k-rows already interpolated at its k (read with zero k-weight).  Also the
+// rows' constants pvc.
 hipError_t launch_small_planet_rows(const rr_tables* t, const double* pv, int32_t npv,
                                     int32_t npar, double k_small, int32_t precision,
-                                    void* rows, hipStream_t s);
+                                    PvConst* pvc, void* rows, hipStream_t s);
 // The same for the log-likelihood's adjoint: row pairs whose k-lerp gives
 // the centre values and whose difference over dk their k-derivative, and
 // 1/I_star per row ([npv][npb]).

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kBlock) void k_pv_prep(const double* __restrict__ m
     const double* row = pv + ipv * npar;
     if (threadIdx.x == kBlock - 1 && pvc && pb == 0)
         pvc[ipv] = make_pv_const<kF32>(row, g.npb, g.k0, k1);
-    if (threadIdx.x == kBlock - 65) ord.mlo[r] = lowest_node(row, sin(row[5]), row[6 + pb], g);
+    if (threadIdx.x == kBlock - 65) ord.mlo[r] = lowest_node(row, row[6 + pb], g);
     for (int j = threadIdx.x; j < nz; j += kBlock) ldp[r * nz + j] = profile_at_bin(mu_s, f, nmu, zm[j]);
     istar_block(mu_s, f, nmu, istar + r, inv_istar + r);
 }
@@ -587,7 +587,7 @@ __device__ inline double sqrt_nr(double x) {
 template <typename R>
 __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
     const double* __restrict__ ze, const double* __restrict__ ldp, const double* __restrict__ pv,
-    const PvConst* __restrict__ pvc, int32_t npar, int64_t nr, int32_t nz, GridDev g,
+    PvConst* __restrict__ pvc, int32_t npar, int64_t nr, int32_t nz, GridDev g,
     R* __restrict__ out) {
     extern __shared__ double direct_lds[];
     double* edge = direct_lds;                     // edges 1 .. nz - 1, at j - 1
@@ -608,7 +608,11 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
     const double k = pv[ipv * npar + 6 + pb];
     __shared__ int low;
     if (threadIdx.x == 64 * kDirectWaves - 1)
-        low = pvc[ipv].flags & kValid ? lowest_node(pv + ipv * npar, pvc[ipv].sinw, k, g) : 0;
+        low = lowest_node(pv + ipv * npar, k, g);
+    // any k in (0, 1]: the smallest positive double as the lower bound
+    if (threadIdx.x == 64 * kDirectWaves - 65 && mb == nmb - 1 && pb == 0)
+        pvc[ipv] = make_pv_const<sizeof(R) == 4>(pv + ipv * npar, g.npb, 4.9406564584124654e-324,
+                                                 1.0);
     __syncthreads();
     if (mb * 64 + 63 < low) return;                // no exposure reads these nodes
     const int m = mb * 64 + lane;
@@ -674,18 +678,22 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
 // precision and in the order the forward kernel combines them.  Workgroup
 // (row, kBlock nodes): a small-planet row stages the mu samples and its
 // passband's profile in LDS (when they fit) for the binary searches.
-// Stored twice ([2][ng]), read with zero k-weight.
+// Stored twice ([2][ng]), read with zero k-weight.  One thread of each row also
+// derives the row's constants pvc for the forward kernel, which took a launch
+// of their own (about 4 us).
 constexpr int kSpLds = 1024;
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_small_planet_rows(
     const double* __restrict__ mu_s, const double* __restrict__ prof, int32_t nmu,
     const R* __restrict__ T, const double* __restrict__ pv, int32_t npar, double k_small,
-    double k1, GridDev g, R* __restrict__ out) {
+    double k1, GridDev g, PvConst* __restrict__ pvc, R* __restrict__ out) {
     __shared__ double smu[kSpLds], sf[kSpLds];
     const int64_t r = blockIdx.x;
     const int m = int(blockIdx.y) * kBlock + int(threadIdx.x);
     const int64_t ipv = r / g.npb;
     const int pb = int(r - ipv * g.npb);
+    if (threadIdx.x == kBlock - 1 && blockIdx.y == 0 && pb == 0)
+        pvc[ipv] = make_pv_const<sizeof(R) == 4>(pv + ipv * npar, g.npb, g.k0, k1, k_small);
     const double k = pv[ipv * npar + 6 + pb];          // uniform in the workgroup
     R* o = out + r * 2 * g.ng;
     R v = R(0);                                        // invalid rows: the forward writes NaN
@@ -719,7 +727,7 @@ __global__ __launch_bounds__(kBlock) void k_small_planet_rows(
     o[g.ng + m] = v;
 }
 
-hipError_t launch_direct_rows(const rr_tables* t, const double* pv, const PvConst* pvc,
+hipError_t launch_direct_rows(const rr_tables* t, const double* pv, PvConst* pvc,
                               int32_t npv, int32_t npar, int32_t precision, void* rows,
                               hipStream_t s) {
     const GridDev g = grid_dev(t);
@@ -829,17 +837,17 @@ hipError_t launch_small_planet_adj_rows(const rr_tables* t, const double* pv, in
 
 hipError_t launch_small_planet_rows(const rr_tables* t, const double* pv, int32_t npv,
                                     int32_t npar, double k_small, int32_t precision,
-                                    void* rows, hipStream_t s) {
+                                    PvConst* pvc, void* rows, hipStream_t s) {
     const GridDev g = grid_dev(t);
     const int64_t nr = int64_t(npv) * t->npb;
     const dim3 grid(unsigned(nr), unsigned((g.ng + kBlock - 1) / kBlock));
     if (precision == RR_FP64)
         hipLaunchKernelGGL(k_small_planet_rows<double>, grid, dim3(kBlock), 0, s, t->mu_s,
-                           t->prof, t->nmu, t->T64, pv, npar, k_small, t->grid.k1, g,
+                           t->prof, t->nmu, t->T64, pv, npar, k_small, t->grid.k1, g, pvc,
                            static_cast<double*>(rows));
     else
         hipLaunchKernelGGL(k_small_planet_rows<float>, grid, dim3(kBlock), 0, s, t->mu_s,
-                           t->prof, t->nmu, t->T32, pv, npar, k_small, t->grid.k1, g,
+                           t->prof, t->nmu, t->T32, pv, npar, k_small, t->grid.k1, g, pvc,
                            static_cast<float*>(rows));
     return hipGetLastError();
 }
