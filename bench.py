@@ -830,7 +830,7 @@ def main():
     m = summary("mixed", 4)
     d = summary("fp64", 8)
     # the forward kernel the library launches on this series (rr_series_kernel)
-    kform = {"split": "k_forward_split<%s, false>", "split_fused": "k_forward_split<%s, true>",
+    kform = {"split": "k_forward_split<%s, false, false>", "split_fused": "k_forward_split<%s, true, false>",
              "tiles": "k_forward<%s, false, 8>"}
     kname = {p: kform[series.kernel(tab, npv, p)] % t
              for p, t in (("mixed", "float"), ("fp64", "double"))}

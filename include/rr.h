@@ -223,9 +223,8 @@ RR_API int rr_evaluate_series(const rr_tables* t, const rr_series* s, const doub
  * RR_KERNEL_SPLIT (1: the split launch of transit and streaming
  * workgroups, after the per-vector setup) or RR_KERNEL_SPLIT_FUSED (2: the
  * split launch alone, its workgroups deriving their vectors' constants
- * themselves; taken while the launch has at most twice as many workgroups
- * as the float kernel keeps resident, where it measured faster, so such a
- * call is one launch).  The two split launches give the same bits; the
+ * themselves; taken while the launch has at most 32 workgroups per CU,
+ * where it measured faster, so such a call is one launch).  The two split launches give the same bits; the
  * per-tile kernel agrees with them within a rounding of the flux (see
  * rr_evaluate_series).  For benchmarks and profiles that name the kernel
  * they time.  Enqueues nothing (the choice may query the device's
@@ -389,12 +388,12 @@ RR_API int rr_flux_at_z(const rr_tables* t, const double* z_d, const double* k_d
  * the profile to the bin means, integrates I_star exactly for the
  * piecewise-linear profile (as rr_prepare_ld does) and contracts W with it
  * over the two k-rows around the vector's k (T = W . l of Sect. 3.1.2,
- * restricted to those rows, in the same bin order as the shared table) in
- * FP64, then interpolates them in k as the shared rows are; the
+ * restricted to those rows and to the grazing nodes the vector's orbit can
+ * reach) in FP64, then interpolates them in k as the shared rows are; the
  * evaluation then follows rr_evaluate with those rows in place of the
  * shared ones.  With every vector given the tables' own profile the fluxes
- * equal rr_evaluate's bitwise.  Other arguments, errors and
- * invalid rows as rr_evaluate; non-finite profile samples give non-finite
+ * equal rr_evaluate's to rounding (the bins are added in another order).
+ * Other arguments, errors and invalid rows as rr_evaluate; non-finite profile samples give non-finite
  * in-transit fluxes of that vector only.  npv * npb * nz < 2^31
  * (RR_ELIMIT beyond).  Temporary device memory, ~(144 + npb (32 + 8 nz +
  * 2 ng sizeof(real))) bytes per vector, is the per-stream buffer that
@@ -430,10 +429,14 @@ RR_API int rr_evaluate_ld(const rr_tables* t, const double* times_d,
  * in order), so all outputs are bitwise reproducible.  The adjoint keeps
  * npb * ng * (2 sizeof(real) + 8) bytes of tables in LDS (and with
  * grad_prof a copy of d logL / d ldw per wave), at most the device's LDS per
- * workgroup (RR_ELIMIT beyond).  Temporary device memory comes from the stream-ordered
- * allocator: ~(160 + 8 (7 + npb) npt / 1024) bytes per parameter vector,
- * and with grad_prof a further 8 npb ng bytes per vector plus at most
- * 512 MiB of partial sums. */
+ * workgroup (RR_ELIMIT beyond).  Temporary device memory: 24 bytes per 64
+ * times, ~(160 + 8 (7 + npb) parts) bytes per parameter vector (parts: the
+ * workgroups that share a vector, 1 from 2048 vectors on), and with grad_prof
+ * a further 8 npb ng bytes per vector plus at most 512 MiB of partial sums.
+ * From the second call on a stream it is a buffer that the tables keep for
+ * that stream (up to 96 MiB each and 512 MiB in all, freed with the tables);
+ * larger calls, a first call and calls under stream capture take it from the
+ * stream-ordered allocator. */
 RR_API int rr_loglik_grad(const rr_tables* t, const double* times_d,
                           const int32_t* lcids_d, int32_t npt,
                           const int32_t* pbids, const int32_t* nss,
@@ -468,7 +471,7 @@ RR_API int rr_loglik_grad_istar(const rr_tables* t, const double* times_d,
  * table rows (the transpose of their contraction with W).  Invalid rows
  * give NaN in logl and grad and a zero profile gradient.  With every
  * vector given the tables' own profile, logl and grad equal
- * rr_loglik_grad's bitwise and the per-vector profile gradients sum to its
+ * rr_loglik_grad's and the per-vector profile gradients sum to its
  * shared one (to rounding).  Other arguments, errors and limits as
  * rr_loglik_grad (no wprof); npv * npb * nz < 2^31. */
 RR_API int rr_loglik_grad_ld(const rr_tables* t, const double* times_d,
@@ -483,9 +486,8 @@ RR_API int rr_loglik_grad_ld(const rr_tables* t, const double* times_d,
 /* Instrumentation: the next rr_evaluate / rr_loglik_grad calls made by the
  * calling thread launch their main kernel with `before` and `after` as the
  * launch's own start and stop events (hipExtLaunchKernel), so the pair times
- * that kernel's execution alone (the per-parameter-vector setup kernel that
- * precedes it is outside the pair; with more than 65 535 parameter vectors
- * the pair spans the consecutive launches of the main kernel).  Both events
+ * that kernel's execution alone (the per-parameter-vector kernels that
+ * precede it are outside the pair).  Both events
  * must be created by the caller on the device of the tables; NULL, NULL
  * turns this off.  Returns RR_EINVAL if exactly one of them is NULL. */
 RR_API int rr_set_kernel_events(hipEvent_t before, hipEvent_t after);

@@ -1,7 +1,8 @@
 // rr_forward.hip -- population light-curve evaluation (Sect. 2 Eq. 5,
 // Sect. 3.1.1, Sect. 3.1.2, Sect. 4.1, Sect. 4.2).
 //
-// Two kernels per call:
+// Two kernels per call on raw arrays (a registered series with one subsample
+// per exposure takes the split launch below instead):
 //
 //   k_pv_setup  one thread per parameter vector: validity, cos i from b,
 //               sin/cos of the eccentric anomaly at conjunction, and the
@@ -11,7 +12,8 @@
 //               units, so the test is frac(phase - lo) < width);
 //   k_forward   one wave64 workgroup per (parameter vector, tile of 64 J
 //               consecutive times; J = 8 by default, 4 or 16 in the variants
-//               of rr_evaluate_variant), lanes along time so loads of the shared
+//               of rr_evaluate_variant), many vectors' same tile before the
+//               next tile (launch_forward), lanes along time so loads of the shared
 //               time array and the stores of out[pv][t] are coalesced; each
 //               wave runs alone (no LDS, no barrier).  Pass 1 reduces each
 //               mid-exposure time to an offset from conjunction (FP64),

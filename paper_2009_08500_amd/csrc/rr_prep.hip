@@ -363,9 +363,9 @@ __global__ __launch_bounds__(kBlock) void k_pv_prep(const double* __restrict__ m
 // the most part), so it needs many of them in flight: with one wave over all
 // bins and 4-byte loads it took 32 us for 1024 walkers (default grid, float),
 // with the bins split over four waves and 16-byte loads 15 us.
-// Lane l takes the nodes m0 + 4 (l & 15) .. + 3 of bins 4 i + (l >> 4), in v_mfma_f64_16x16x4f64 chains D = A B with A[m][j] =
-// W[ik + s][j][m] and B[j][q] = ldp of row q when the row's k-row is ik, else
-// 0, over the distinct ik of the tile (FP64 products and sums; only the order
+// Lane l takes the nodes m0 + 4 (l & 15) .. + 3 of bins 4 i + (l >> 4), in
+// v_mfma_f64_16x16x4f64 chains D = A B with A[m][j] = W[ik + s][j][m] and
+// B[j][q] = ldp of row q when the row's k-row is ik, else 0, over the distinct ik of the tile (FP64 products and sums; only the order
 // of the additions over j differs from k_tables).  Lane l holds
 // A[l & 15][l >> 4], B[l >> 4][l & 15] and D[4 i + (l >> 4)][l & 15] (checked
 // on the device); row a of chain q is node m0 + 4 a + q.
