@@ -1000,7 +1000,8 @@ __device__ inline double row_ak(const double* __restrict__ pv, int32_t npar, int
 
 // Tile rt, bins j0 .. j0 + 15: D[j][q] = sum_m W[ik][j][m] (1 - ak_q) g_q[m] +
 // W[ik+1][j][m] ak_q g_q[m] (g_q = dlogL/dldw of row q, zero for rows on
-// another k-row), v_mfma_f64_16x16x4f64 chains into one accumulator.  Lane l
+// another k-row: selected, not multiplied, since row 0, which such a column
+// loads, may hold NaN), v_mfma_f64_16x16x4f64 chains into one accumulator.  Lane l
 // holds A row / B column l & 15; the k index of step u is node
 // m + 4 (l >> 4) + u, so a lane's 16-byte load feeds four steps.
 template <bool kVec, typename WT>
@@ -1024,7 +1025,7 @@ __device__ inline void pv_ldp_grad_mfma(const WT* __restrict__ W, const double* 
         const WT* w0 = W + (int64_t(cur) * nz + jj) * g.ng;
         const WT* w1 = w0 + int64_t(nz) * g.ng;
         const double* gr = gldw + (take ? r : 0) * g.ng;
-        const double f0 = take ? 1.0 - ak : 0.0, f1 = take ? ak : 0.0;
+        const double f0 = 1.0 - ak, f1 = ak;
         constexpr int kStep = 2;
         for (int m0 = first + 16 * wave; m0 < g.ng; m0 += 16 * kLdpWaves * kStep) {
             WT a0[kStep][4], a1[kStep][4];
@@ -1040,8 +1041,9 @@ __device__ inline void pv_ldp_grad_mfma(const WT* __restrict__ W, const double* 
             for (int u = 0; u < kStep; ++u)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a0[u][q]), f0 * b[u][q], d, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a1[u][q]), f1 * b[u][q], d, 0, 0, 0);
+                    const double gq = take ? b[u][q] : 0.0;
+                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a0[u][q]), f0 * gq, d, 0, 0, 0);
+                    d = __builtin_amdgcn_mfma_f64_16x16x4f64(double(a1[u][q]), f1 * gq, d, 0, 0, 0);
                 }
         }
         cur = wave_min(ik > cur ? ik : 0x7fffffff);
