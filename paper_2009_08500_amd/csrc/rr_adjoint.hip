@@ -995,7 +995,7 @@ __device__ inline double row_ak(const double* __restrict__ pv, int32_t npar, int
                                 const GridDev& g) {
     const int64_t ipv = r / g.npb;
     const double ak = (pv[ipv * npar + 6 + int(r - ipv * g.npb)] - g.k0) / g.dk - ik;
-    return ak == ak ? ak : 0.0;
+    return is_finite(ak) ? ak : 0.0;
 }
 
 // Tile rt, bins j0 .. j0 + 15: D[j][q] = sum_m W[ik][j][m] (1 - ak_q) g_q[m] +
