@@ -171,7 +171,11 @@ RR_API int rr_set_istar(rr_tables* t, const double* istar_d, hipStream_t stream)
  * Temporary device memory (144 bytes per parameter vector) is a per-stream
  * buffer kept by the tables handle: it grows (with a synchronising
  * reallocation) when a call needs more, is reused without waiting by later
- * calls on the same stream, and is freed by rr_free_tables. */
+ * calls on the same stream, and is freed by rr_free_tables.  A stream is
+ * known by its handle: let the calls on it finish before it is destroyed, or
+ * a new stream that gets the same handle may share their buffer.  On
+ * hipStreamPerThread, one handle for every thread's stream, nothing is kept:
+ * each call's memory comes from the stream-ordered allocator. */
 RR_API int rr_evaluate(const rr_tables* t, const double* times_d,
                        const int32_t* lcids_d, int32_t npt,
                        const int32_t* pbids, const int32_t* nss,
@@ -434,9 +438,10 @@ RR_API int rr_evaluate_ld(const rr_tables* t, const double* times_d,
  * workgroups that share a vector, 1 from 2048 vectors on), and with grad_prof
  * a further 8 npb ng bytes per vector plus at most 512 MiB of partial sums.
  * From the second call on a stream it is a buffer that the tables keep for
- * that stream (up to 96 MiB each and 512 MiB in all, freed with the tables);
- * larger calls, a first call and calls under stream capture take it from the
- * stream-ordered allocator. */
+ * that stream, under rr_evaluate's rule for destroyed streams (up to 96 MiB
+ * each and 512 MiB in all, freed with the tables); larger calls, a first
+ * call, calls on hipStreamPerThread and calls under stream capture take it
+ * from the stream-ordered allocator. */
 RR_API int rr_loglik_grad(const rr_tables* t, const double* times_d,
                           const int32_t* lcids_d, int32_t npt,
                           const int32_t* pbids, const int32_t* nss,

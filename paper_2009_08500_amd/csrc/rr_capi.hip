@@ -71,7 +71,39 @@ static int check_grid(const rr_grid* g) {
     return RR_OK;
 }
 
-hipError_t stream_workspace(rr_tables* t, hipStream_t stream, size_t bytes, void** out) {
+// Buffers are kept by stream handle, for the work of one stream is ordered.
+// hipStreamPerThread is one handle for a different stream in every thread, so
+// nothing is kept for it.
+static bool keeps_buffers(hipStream_t stream) { return stream != hipStreamPerThread; }
+
+// Memory of one call from the stream-ordered allocator, given back behind the
+// work that the call has enqueued.
+class StreamMemory {
+  public:
+    hipError_t alloc(hipStream_t stream, size_t bytes, void** out) {
+        stream_ = stream;
+        const hipError_t e = hipMallocAsync(&p_, bytes, stream);
+        if (e != hipSuccess) p_ = nullptr;
+        *out = p_;
+        return e;
+    }
+    hipError_t release() {
+        void* p = p_;
+        p_ = nullptr;
+        return p ? hipFreeAsync(p, stream_) : hipSuccess;
+    }
+    ~StreamMemory() { (void)release(); }
+
+  private:
+    hipStream_t stream_ = nullptr;
+    void* p_ = nullptr;
+};
+
+// Device workspace of at least `bytes` for `stream`: the buffer that the
+// tables keep for it, or memory of the call in `own`.
+static hipError_t stream_workspace(rr_tables* t, hipStream_t stream, size_t bytes,
+                                   StreamMemory* own, void** out) {
+    if (!keeps_buffers(stream)) return own->alloc(stream, bytes, out);
     std::lock_guard<std::mutex> lk(t->ws_mu);
     auto& slot = t->ws[stream];
     if (slot.second < bytes) {
@@ -96,17 +128,20 @@ hipError_t stream_workspace(rr_tables* t, hipStream_t stream, size_t bytes, void
 // the call is large, the kept buffers would be too many, or the stream is
 // being captured (a graph must own what it reads), and for the first call on
 // a stream (tables used once: 20 MB of new memory take longer to map than
-// the pool's to reuse).  Allocating and freeing on
-// every call cost 12 us of host time: 100 walkers x 8000 x 2 in float, per
-// call, 37 -> 25 us.
+// the pool's to reuse).  Allocating and freeing on every call costs 15 us of
+// a small call and keeps the host waiting in a large one (10 walkers x 1000 in
+// float, per call, 40 -> 25 us; 1024 x 50 000 x 5 in FP64 with the profile
+// gradient 210 -> 206, of it on the host 206 -> 33).  A memory pool of the
+// tables' own that holds on to its memory costs as much as the device's
+// (39, 209 and 205), and an event to order each use behind the last, whatever
+// the handle names, 1-3 us and 15 us of a call that is waited for.
 class CallMemory {
   public:
-    hipError_t take(rr_tables* t, hipStream_t stream, size_t bytes, char** out) {
-        stream_ = stream;
+    hipError_t take(rr_tables* t, hipStream_t stream, size_t bytes, void** out) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         hipError_t e = hipStreamIsCapturing(stream, &cap);
         if (e != hipSuccess) return e;
-        if (cap == hipStreamCaptureStatusNone && bytes <= kKeepBytes) {
+        if (cap == hipStreamCaptureStatusNone && bytes <= kKeepBytes && keeps_buffers(stream)) {
             lk_ = std::unique_lock<std::mutex>(t->lk_mu);
             const bool again = t->lk.count(stream) != 0;    // a first call keeps nothing
             auto& slot = t->lk[stream];
@@ -122,28 +157,21 @@ class CallMemory {
                 if (grown && (e = hipFreeAsync(grown, stream)) != hipSuccess) return e;
             }
             if (slot.second >= bytes) {
-                *out = static_cast<char*>(slot.first);
+                *out = slot.first;
                 return hipSuccess;
             }
             lk_.unlock();
         }
-        e = hipMallocAsync(&own_, bytes, stream);
-        if (e != hipSuccess) own_ = nullptr;
-        *out = static_cast<char*>(own_);
-        return e;
+        return own_.alloc(stream, bytes, out);
     }
     hipError_t release() {
         if (lk_.owns_lock()) lk_.unlock();
-        void* p = own_;
-        own_ = nullptr;
-        return p ? hipFreeAsync(p, stream_) : hipSuccess;
+        return own_.release();
     }
-    ~CallMemory() { (void)release(); }
 
   private:
     std::unique_lock<std::mutex> lk_;
-    hipStream_t stream_ = nullptr;
-    void* own_ = nullptr;
+    StreamMemory own_;
 };
 
 static void free_tables(rr_tables* t) {
@@ -363,8 +391,9 @@ RR_API int rr_evaluate(const rr_tables* t, const double* times_d,
     rc = check_device(t);
     if (rc) return rc;
     void* ws = nullptr;
+    StreamMemory own;
     hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream,
-                                    sizeof(PvConst) * size_t(npv), &ws);
+                                    sizeof(PvConst) * size_t(npv), &own, &ws);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
     PvConst* pvc = static_cast<PvConst*>(ws);
     e = launch_pv_setup(t, pv_d, npv, npar, pvc, precision, stream);
@@ -501,10 +530,11 @@ RR_API int rr_evaluate_series(const rr_tables* t, const rr_series* se, const dou
     const SplitPlan sp = split ? plan_forward_split(se, npv, precision) : SplitPlan{};
     hipError_t e = hipSuccess;
     PvConst* pvc = nullptr;
+    StreamMemory own;
     if (!(split && sp.self_setup)) {
         void* ws = nullptr;
         e = stream_workspace(const_cast<rr_tables*>(t), stream, sizeof(PvConst) * size_t(npv),
-                             &ws);
+                             &own, &ws);
         if (e != hipSuccess)
             return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
         pvc = static_cast<PvConst*>(ws);
@@ -559,8 +589,9 @@ RR_API int rr_evaluate_variant(const rr_tables* t, const double* times_d,
     rc = check_device(t);
     if (rc) return rc;
     void* ws = nullptr;
+    StreamMemory own;
     hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream,
-                                    sizeof(PvConst) * size_t(npv), &ws);
+                                    sizeof(PvConst) * size_t(npv), &own, &ws);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
     PvConst* pvc = static_cast<PvConst*>(ws);
     e = launch_pv_setup(t, pv_d, npv, npar, pvc, precision, stream);
@@ -592,8 +623,9 @@ RR_API int rr_select_variant(const rr_tables* t, const double* times_d,
     rc = check_device(t);
     if (rc) return rc;
     void* ws = nullptr;
+    StreamMemory own;
     hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream,
-                                    sizeof(PvConst) * size_t(npv), &ws);
+                                    sizeof(PvConst) * size_t(npv), &own, &ws);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
     PvConst* pvc = static_cast<PvConst*>(ws);
     e = launch_pv_setup(t, pv_d, npv, npar, pvc, precision, stream);
@@ -659,7 +691,8 @@ RR_API int rr_evaluate_direct(const rr_tables* t, const double* times_d,
     const size_t o_pvc = take(sizeof(PvConst) * size_t(npv));
     const size_t o_rows = take(elt * size_t(nr) * 2 * t->grid.ng);
     void* ws = nullptr;
-    hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream, off, &ws);
+    StreamMemory own;
+    hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream, off, &own, &ws);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
     char* base = static_cast<char*>(ws);
     PvConst* pvc = reinterpret_cast<PvConst*>(base + o_pvc);
@@ -696,7 +729,8 @@ RR_API int rr_evaluate_small_planet(const rr_tables* t, const double* times_d,
     const size_t o_pvc = take(sizeof(PvConst) * size_t(npv));
     const size_t o_rows = take(elt * size_t(nr) * 2 * t->grid.ng);
     void* ws = nullptr;
-    hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream, off, &ws);
+    StreamMemory own;
+    hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream, off, &own, &ws);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
     char* base = static_cast<char*>(ws);
     PvConst* pvc = reinterpret_cast<PvConst*>(base + o_pvc);
@@ -757,7 +791,8 @@ RR_API int rr_evaluate_ld(const rr_tables* t, const double* times_d,
     // the tables' per-stream workspace (as rr_evaluate): reused without
     // waiting by later calls on the same stream
     void* ws = nullptr;
-    hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream, off, &ws);
+    StreamMemory own;
+    hipError_t e = stream_workspace(const_cast<rr_tables*>(t), stream, off, &own, &ws);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "workspace");
     char* base = static_cast<char*>(ws);
     PvConst* pvc = reinterpret_cast<PvConst*>(base + o_pvc);
@@ -877,10 +912,11 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
     const size_t o_sgw = segs ? take(sizeof(double) * size_t(npv) * nseg * t->npb * g.ng) : 0;
     const size_t o_sgi = segs ? take(sizeof(double) * size_t(npv) * nseg * t->npb) : 0;
     const size_t o_sfl = segs ? take(sizeof(int32_t) * size_t(npv) * nseg) : 0;
-    char* base = nullptr;
+    void* mem_d = nullptr;
     CallMemory mem;
-    e = mem.take(const_cast<rr_tables*>(t), stream, off, &base);
+    e = mem.take(const_cast<rr_tables*>(t), stream, off, &mem_d);
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? RR_ENOMEM : hip_fail(e, "temporaries");
+    char* base = static_cast<char*>(mem_d);
     AdjointArgs A;
     A.times = times_d; A.lcids = lcids_d; A.npt = npt; A.lc = &lc; A.pv = pv_d;
     A.npv = npv; A.npar = npar; A.pvc = reinterpret_cast<PvConst*>(base + o_pvc); A.g = g;

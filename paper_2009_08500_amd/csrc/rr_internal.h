@@ -204,7 +204,8 @@ struct rr_tables {
     double* istar_user = nullptr;
     bool istar_fixed = false;
     // Per-stream temporaries of rr_evaluate (grow-only; work on one stream is
-    // ordered, so a stream's buffer is reused without waiting).
+    // ordered, so a stream's buffer is reused without waiting; none for
+    // hipStreamPerThread, which is a stream of each thread's).
     std::mutex ws_mu;
     std::unordered_map<hipStream_t, std::pair<void*, size_t>> ws;
     // The same for the log-likelihood (a call's buffer is its own until the
@@ -235,8 +236,6 @@ inline void launch_timed(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_
 }
 int hip_fail(hipError_t err, const char* what);
 constexpr size_t kKeepBytes = size_t(96) << 20, kKeepTotal = size_t(512) << 20;
-// Device workspace of at least `bytes` for `stream`, owned by the tables.
-hipError_t stream_workspace(rr_tables* t, hipStream_t stream, size_t bytes, void** out);
 rr::GridDev grid_dev(const rr_tables* t);
 
 // Kernel launchers (rr_prep.hip, rr_forward.hip).
