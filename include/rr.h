@@ -395,10 +395,11 @@ RR_API int rr_flux_at_z(const rr_tables* t, const double* z_d, const double* k_d
  * restricted to those rows and to the grazing nodes the vector's orbit can
  * reach) in FP64, then interpolates them in k as the shared rows are; the
  * evaluation then follows rr_evaluate with those rows in place of the
- * shared ones.  With every vector given the tables' own profile the fluxes
- * equal rr_evaluate's to rounding (the bins are added in another order).
- * Other arguments, errors and invalid rows as rr_evaluate; non-finite profile samples give non-finite
- * in-transit fluxes of that vector only.  npv * npb * nz < 2^31
+ * shared ones.  With every vector given the tables' own profile the FP64
+ * fluxes equal rr_evaluate's bitwise (mixed: to rounding, since the vectors'
+ * rows come from the FP32 copy of W).  Other arguments, errors and invalid
+ * rows as rr_evaluate; non-finite profile samples give non-finite in-transit
+ * fluxes of that vector only.  npv * npb * nz < 2^31
  * (RR_ELIMIT beyond).  Temporary device memory, ~(144 + npb (32 + 8 nz +
  * 2 ng sizeof(real))) bytes per vector, is the per-stream buffer that
  * rr_evaluate uses (same growth and reuse rules). */
@@ -476,8 +477,8 @@ RR_API int rr_loglik_grad_istar(const rr_tables* t, const double* times_d,
  * table rows (the transpose of their contraction with W).  Invalid rows
  * give NaN in logl and grad and a zero profile gradient.  With every
  * vector given the tables' own profile, logl and grad equal
- * rr_loglik_grad's and the per-vector profile gradients sum to its
- * shared one (to rounding).  Other arguments, errors and limits as
+ * rr_loglik_grad's (in FP64 bitwise, mixed to rounding) and the per-vector
+ * profile gradients sum to its shared one (to rounding).  Other arguments, errors and limits as
  * rr_loglik_grad (no wprof); npv * npb * nz < 2^31. */
 RR_API int rr_loglik_grad_ld(const rr_tables* t, const double* times_d,
                              const int32_t* lcids_d, int32_t npt,

@@ -600,4 +600,19 @@ __device__ inline void load4(const T* __restrict__ w, int m, int n, T* x) {
     }
 }
 
+// The same for two consecutive doubles from element m (even).
+template <bool kVec>
+__device__ inline void load_pair(const double* __restrict__ w, int m, int n, double* x) {
+    const bool in0 = m < n, in1 = m + 1 < n;
+    if constexpr (kVec) {
+        const double2 v = *reinterpret_cast<const double2*>(w + (in0 ? m : 0));
+        x[0] = in0 ? v.x : 0.0;
+        x[1] = in0 ? v.y : 0.0;
+    } else {
+        const double v0 = w[in0 ? m : 0], v1 = w[in1 ? m + 1 : 0];
+        x[0] = in0 ? v0 : 0.0;
+        x[1] = in1 ? v1 : 0.0;
+    }
+}
+
 }  // namespace rr

@@ -357,16 +357,17 @@ __global__ __launch_bounds__(kBlock) void k_pv_prep(const double* __restrict__ m
 // s = 0, 1.  Rows of a sorted 16-row tile with at most two distinct k-rows go
 // to the matrix cores (each W value read once for up to 16 rows); the rows of
 // the other tiles (k spread over many k-rows, where a tile would need a pass
-// per k-row) one by one.  The two parts share one launch of workgroups of 64
-// nodes (m) and four waves that split the bins; nodes below lowest_node are
-// left out.  Matrix cores: the part waits on its loads of W (from the L2 for
-// the most part), so it needs many of them in flight: with one wave over all
-// bins and 4-byte loads it took 32 us for 1024 walkers (default grid, float),
-// with the bins split over four waves and 16-byte loads 15 us.
-// Lane l takes the nodes m0 + 4 (l & 15) .. + 3 of bins 4 i + (l >> 4), in
+// per k-row) one by one.  The two parts share one launch; nodes below
+// lowest_node are left out.  Matrix cores: the part waits on its loads of W
+// (from the L2 for the most part), so it needs many of them in flight: with
+// one wave over all bins and 4-byte loads it took 32 us for 1024 walkers
+// (default grid, float), with the bins split over four waves and 16-byte loads
+// 15 us.
+// FP32 weights, workgroups of 64 nodes and four waves that split the bins:
+// lane l takes the nodes m0 + 4 (l & 15) .. + 3 of bins 4 i + (l >> 4), in
 // v_mfma_f64_16x16x4f64 chains D = A B with A[m][j] = W[ik + s][j][m] and
-// B[j][q] = ldp of row q when the row's k-row is ik, else 0, over the distinct ik of the tile (FP64 products and sums; only the order
-// of the additions over j differs from k_tables).  Lane l holds
+// B[j][q] = ldp of row q when the row's k-row is ik, else 0, over the distinct
+// ik of the tile (FP64 products and sums).  Lane l holds
 // A[l & 15][l >> 4], B[l >> 4][l & 15] and D[4 i + (l >> 4)][l & 15] (checked
 // on the device); row a of chain q is node m0 + 4 a + q.
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -445,79 +446,110 @@ __device__ inline void pv_tables_mfma(const WT* __restrict__ W, const double* __
         }
 }
 
-// One sorted row, one node per lane: wave w takes part w % kRowSplit of the
-// bins of the 64 nodes at m0 + 64 (w / kRowSplit), and the parts are added in
-// order.  What bounds it is the traffic of the distinct W rows into the eight
-// L2s (53 MB in float, 106 MB in FP64 for a population of 512): the split and
-// the loads in flight only have to keep that busy (float 18.2 us unsplit with
-// 40 loads in flight, 20.0 split by 4; FP64 45.9 and 42.0).
-template <typename WT>
-constexpr int kRowSplit = sizeof(WT) == 4 ? 1 : 4;
-template <typename WT>
-constexpr int kRowNodes = kPvNodes * kPvWaves / kRowSplit<WT>;   // per workgroup
-template <typename R, typename WT>
-__device__ inline void pv_tables_row(const WT* __restrict__ W, const double* __restrict__ ldp,
-                                     const PvOrder& ord, int64_t pos, int32_t nz,
-                                     const GridDev& g, R* __restrict__ out, int m0,
-                                     double* __restrict__ lds) {
-    constexpr int kSplit = kRowSplit<WT>;
-    const int64_t r = ord.perm[pos];
-    const int ik = ord.key[pos];
-    const int mlo = ord.mlo[r];
-    if (mlo >= m0 + kRowNodes<WT>) return;             // uniform
+// The same for FP64 weights with the bins in order, so that a row given the
+// tables' own profile has k_tables' bits (the matrix core adds its products in
+// order, as a chain of FMAs): wave w takes table row s = w & 1 of the nodes
+// m0 + 32 (w >> 1) .. + 31, lane l nodes 2 (l & 15) and the next, and two
+// chains run over all bins.  Calls of 1024 x 20 000 walkers 64 us (62 with the
+// bins split as above, 66 with one node per lane and 8-byte loads), of 4096 x
+// 1000 88 (96, 96).
+template <bool kVec, typename R>
+__device__ inline void pv_tables_mfma_ordered(const double* __restrict__ W,
+                                              const double* __restrict__ ldp, const PvOrder& ord,
+                                              int64_t nr, int32_t nz, const GridDev& g,
+                                              R* __restrict__ out, int64_t rt, int m0) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    const int part = wave % kSplit;
-    const int mw = m0 + wave / kSplit * kPvNodes, m = mw + lane;
-    double a0 = 0.0, a1 = 0.0;
-    if (mw < g.ng && mlo < mw + kPvNodes) {
-        const WT* w0 = W + int64_t(ik) * nz * g.ng + (m < g.ng ? m : 0);
-        const WT* w1 = w0 + int64_t(nz) * g.ng;
-        const double* lr = ldp + r * nz;           // uniform
-        const int per = (nz + kSplit - 1) / kSplit;
-        const int j1 = min(nz, per * (part + 1));
-        constexpr int kStep = kSplit == 1 ? 20 : 9;     // bins in flight
-        int j = per * part;
-        for (; j + kStep <= j1; j += kStep) {
-            WT x0[kStep], x1[kStep];
+    const int ka = lane >> 4, col = lane & 15, s = wave & 1;
+    const int64_t pos = rt * kTileRows + col;
+    const int64_t r = pos < nr ? ord.perm[pos] : -1;
+    const int ik = pos < nr ? ord.key[pos] : 0x7fffffff;
+    const int mw = m0 + 32 * (wave >> 1);
+    if (mw >= g.ng || wave_min(r >= 0 ? ord.mlo[r] : g.ng) >= mw + 32) return;   // uniform
+    const int mm = mw + 2 * col;
+    v4d d0 = {0.0, 0.0, 0.0, 0.0}, d1 = {0.0, 0.0, 0.0, 0.0};
+    int cur = wave_min(ik);
+    while (cur != 0x7fffffff) {
+        const bool take = ik == cur;
+        const double* w = W + int64_t(cur + s) * nz * g.ng;
+        const double* lr = ldp + (take ? r : 0) * nz;
+        constexpr int kStep = 8;                    // steps of four bins in flight
+        for (int j0 = ka; j0 - ka < nz; j0 += 4 * kStep) {
+            double a[kStep][2], b[kStep];
 #pragma unroll
-            for (int b = 0; b < kStep; ++b) {
-                x0[b] = w0[int64_t(j + b) * g.ng];
-                x1[b] = w1[int64_t(j + b) * g.ng];
+            for (int u = 0; u < kStep; ++u) {
+                const int j = j0 + 4 * u, jc = j < nz ? j : nz - 1;
+                load_pair<kVec>(w + int64_t(jc) * g.ng, mm, g.ng, a[u]);
+                const double bj = lr[jc];
+                b[u] = j < nz && take ? bj : 0.0;
             }
 #pragma unroll
-            for (int b = 0; b < kStep; ++b) {
-                a0 += double(x0[b]) * lr[j + b];
-                a1 += double(x1[b]) * lr[j + b];
+            for (int u = 0; u < kStep; ++u) {
+                d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][0], b[u], d0, 0, 0, 0);
+                d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][1], b[u], d1, 0, 0, 0);
             }
         }
-        for (; j < j1; ++j) {
-            a0 += double(w0[int64_t(j) * g.ng]) * lr[j];
-            a1 += double(w1[int64_t(j) * g.ng]) * lr[j];
-        }
+        cur = wave_min(ik > cur ? ik : 0x7fffffff);
     }
-    if constexpr (kSplit > 1) {
-        if (part > 0) {
-            lds[wave * 128 + lane] = a0;
-            lds[wave * 128 + 64 + lane] = a1;
-        }
-        __syncthreads();
-        if (part > 0) return;
+    if (r < 0) return;
+    R* o = out + (r * 2 + s) * g.ng;
 #pragma unroll
-        for (int w = 1; w < kSplit; ++w) {
-            a0 += lds[(wave + w) * 128 + lane];
-            a1 += lds[(wave + w) * 128 + 64 + lane];
-        }
-    }
-    if (m < g.ng && mlo < mw + kPvNodes) {
-        R* o = out + r * 2 * g.ng + m;
-        o[0] = R(a0);
-        o[g.ng] = R(a1);
+    for (int i = 0; i < 4; ++i) {
+        const int m = mw + 2 * (4 * i + ka);
+        if (m < g.ng) o[m] = R(d0[i]);
+        if (m + 1 < g.ng) o[m + 1] = R(d1[i]);
     }
 }
 
+// One sorted row, one node per lane, the bins in order (k_tables' bits, as
+// above).  What bounds it is the traffic of the distinct W rows into the eight
+// L2s (53 MB in float, 106 MB in FP64 for a population of 512): the loads in
+// flight only have to keep that busy (float 18.2 us with 40 of them).  In FP64
+// a wave takes one of the two table rows, so that few rows still keep enough
+// loads in flight (a call of 37 rows x 5000 32 us with both, 26 with one; 512 x
+// 20 000 78 and 77, 75 with the bins split over four waves, whose order is
+// another).
+template <typename WT>
+constexpr int kRowTabs = sizeof(WT) == 4 ? 2 : 1;                 // table rows per wave
+template <typename WT>
+constexpr int kRowNodes = kPvNodes * kPvWaves * kRowTabs<WT> / 2; // per workgroup
+template <typename R, typename WT>
+__device__ inline void pv_tables_row(const WT* __restrict__ W, const double* __restrict__ ldp,
+                                     const PvOrder& ord, int64_t pos, int32_t nz,
+                                     const GridDev& g, R* __restrict__ out, int m0) {
+    constexpr int kTabs = kRowTabs<WT>;
+    const int64_t r = ord.perm[pos];
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int mw = m0 + wave * kTabs / 2 * kPvNodes, m = mw + int(threadIdx.x & 63);
+    if (mw >= g.ng || ord.mlo[r] >= mw + kPvNodes) return;     // uniform
+    const int s0 = kTabs == 2 ? 0 : wave & 1;                  // first table row
+    const WT* w = W + int64_t(ord.key[pos] + s0) * nz * g.ng + (m < g.ng ? m : 0);
+    const int64_t next = int64_t(nz) * g.ng;                   // the k-row above
+    const double* lr = ldp + r * nz;                           // uniform
+    double acc[kTabs] = {};
+    constexpr int kStep = 20;               // bins in flight
+    int j = 0;
+    for (; j + kStep <= nz; j += kStep) {
+        WT x[kTabs][kStep];
+#pragma unroll
+        for (int b = 0; b < kStep; ++b)
+#pragma unroll
+            for (int s = 0; s < kTabs; ++s) x[s][b] = w[s * next + int64_t(j + b) * g.ng];
+#pragma unroll
+        for (int b = 0; b < kStep; ++b)
+#pragma unroll
+            for (int s = 0; s < kTabs; ++s) acc[s] += double(x[s][b]) * lr[j + b];
+    }
+    for (; j < nz; ++j)
+#pragma unroll
+        for (int s = 0; s < kTabs; ++s) acc[s] += double(w[s * next + int64_t(j) * g.ng]) * lr[j];
+    if (m < g.ng)
+#pragma unroll
+        for (int s = 0; s < kTabs; ++s) out[(r * 2 + s0 + s) * g.ng + m] = R(acc[s]);
+}
+
 // Workgroups [0, n_mfma) take (tile, 64 nodes) on the matrix cores, the
-// others (sorted row, 64 nodes): those in an XCD-aware order -- blocks go
+// others (sorted row, kRowNodes nodes): those in an XCD-aware order -- blocks go
 // round-robin to the eight XCDs, so block p works on item (p mod 8) *
 // (blocks / 8) + p / 8 (rounded for a remainder; n_mfma is a multiple of 8)
 // and each XCD walks a contiguous stretch of the sorted rows, whose W rows
@@ -529,14 +561,19 @@ __global__ __launch_bounds__(kBlock, 3) void k_pv_tables(const WT* __restrict__ 
                                                       PvOrder ord, int64_t nr, int32_t nz,
                                                       GridDev g, int64_t n_mfma,
                                                       int64_t blocks, R* __restrict__ out) {
-    __shared__ double lds[kPvLds];
     const int64_t b = flat_block();
     if (b >= blocks) return;
     const int nmb = (g.ng + kPvNodes - 1) / kPvNodes;
     if (b < n_mfma) {
         const int64_t rt = b / nmb;
         if (rt * kTileRows >= nr || !ord.mfma[rt]) return;
-        pv_tables_mfma<kVec, R, WT>(W, ldp, ord, nr, nz, g, out, rt, int(b - rt * nmb) * kPvNodes, lds);
+        const int m0 = int(b - rt * nmb) * kPvNodes;
+        if constexpr (sizeof(WT) == 8) {
+            pv_tables_mfma_ordered<kVec, R>(W, ldp, ord, nr, nz, g, out, rt, m0);
+        } else {
+            __shared__ double lds[kPvLds];
+            pv_tables_mfma<kVec, R, WT>(W, ldp, ord, nr, nz, g, out, rt, m0, lds);
+        }
         return;
     }
     const int64_t nb = blocks - n_mfma, p = b - n_mfma;
@@ -545,7 +582,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_pv_tables(const WT* __restrict__ 
     const int nrb = (g.ng + kRowNodes<WT> - 1) / kRowNodes<WT>;
     const int64_t pos = L / nrb;
     if (ord.mfma[pos / kTileRows]) return;
-    pv_tables_row<R, WT>(W, ldp, ord, pos, nz, g, out, int(L - pos * nrb) * kRowNodes<WT>, lds);
+    pv_tables_row<R, WT>(W, ldp, ord, pos, nz, g, out, int(L - pos * nrb) * kRowNodes<WT>);
 }
 
 // Direct model (Sect. 3.1.1): the LD-weighted vector of row r = (vector,
