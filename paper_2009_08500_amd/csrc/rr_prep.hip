@@ -638,10 +638,17 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
     const int pb = int(r - ipv * g.npb);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const double* l = ldp + int64_t(pb) * nz;
+    bool finite = is_finite(l[0]);
     for (int j = 1 + threadIdx.x; j < nz; j += 64 * kDirectWaves) {
         edge[j - 1] = ze[j];
         dl[j - 1] = l[j] - l[j - 1];
+        finite = finite && is_finite(l[j]);
     }
+    // the sum over all bins that this stands for is not finite wherever a bin
+    // is not, also in nodes whose planet does not reach that bin
+    __shared__ int prof_ok[kDirectWaves];
+    const int wave_ok = __all(finite);
+    if (lane == 0) prof_ok[wave] = wave_ok;
     const double k = pv[ipv * npar + 6 + pb];
     __shared__ int low;
     if (threadIdx.x == 64 * kDirectWaves - 1)
@@ -701,6 +708,8 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct_rows(
         // the planet, A_J = tot = pi k^2
         const double tot = lens_area<double>(1.0, k, c);
         acc = tot > 0.0 ? l[J - 1] - s / tot : l[nz - 1];
+#pragma unroll
+        for (int w = 0; w < kDirectWaves; ++w) acc = prof_ok[w] ? acc : double(NAN);
     }
     o[m] = R(acc);
     o[g.ng + m] = R(acc);
