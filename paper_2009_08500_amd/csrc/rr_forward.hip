@@ -736,19 +736,20 @@ __device__ inline const LcInfo& stage_lc(const LcInfo& lc, LcInfo* lds) {
 }
 
 // One population (rr_evaluate): row pv0 + r, tile x of 64 J times.  kSubPar:
-// some light curve has nss > 1.  Within a run of job.row_run rows the rows run
-// fastest (see launch_forward).
+// some light curve has nss > 1.  Run (y, z) of job.row_run rows, in which the
+// rows run fastest (see launch_forward).
 template <typename R, bool kSubPar, int J>
 __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdJob job, LcInfo lc, GridDev g,
                                                     const R* __restrict__ T,
                                                     const double* __restrict__ inv_istar) {
-    const int64_t b = flat_block();
-    const int64_t per = int64_t(job.row_run) * job.ntiles;    // workgroups of a run of rows
-    const int r0 = int(b / per) * job.row_run;
+    const int r0 = int(blockIdx.z * gridDim.y + blockIdx.y) * job.row_run;
     if (r0 >= job.npv) return;
     const int rows = min(job.row_run, job.npv - r0);
-    const int local = int(b - int64_t(r0) * job.ntiles);
-    const int tile = local / rows;
+    const int local = int(blockIdx.x);
+    // A quotient comes out of vector registers.  Left there, the row's index and
+    // all that hangs on it took 129 of them in FP64 instead of 123, so three
+    // waves per SIMD instead of four (1024 x 50 000 at nss 5: 197 and 180 us).
+    const int tile = rows == 1 ? local : __builtin_amdgcn_readfirstlane(local / rows);
     if (tile >= job.ntiles) return;
     const int ipv = job.pv0 + r0 + (local - tile * rows);
     if constexpr (kSubPar) {
@@ -881,10 +882,18 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
     // write more rows at a time than suits memory: 64 rows at nss 1 (512 x
     // 60 000: 38.5 -> 36.7, 64.6 -> 57.8; with 256 rows FP64 takes 66.1), and
     // row by row when supersampled, where tiles of all kinds mixed serve better
-    // (512 rows at nss 5: 38.9 and 67.1; with 64 rows 38.7 and 71.5).
+    // (512 rows at nss 5: 38.9 and 67.1; with 64 rows 38.7 and 71.5).  The runs
+    // are of nearly equal length, one per grid row, since dividing a flat index
+    // costs every wave of a large launch (1024 x 50 000 at nss 5 in float 103,
+    // 99 us this way).
     const int64_t waves = int64_t(job.ntiles) * npv;
-    job.row_run = waves <= 24576 ? 256 : (sub ? 1 : 64);
-    const dim3 grid = flat_grid(waves), block(kFwdBlock);
+    const int64_t most = waves <= 24576 ? 256 : (sub ? 1 : 64);
+    const int64_t runs = (npv + most - 1) / most;
+    job.row_run = int32_t((npv + runs - 1) / runs);
+    const int64_t gy = std::min<int64_t>(runs, 65535);
+    const dim3 grid(unsigned(int64_t(job.row_run) * job.ntiles), unsigned(gy),
+                    unsigned((runs + gy - 1) / gy));
+    const dim3 block(kFwdBlock);
     const hipError_t e =
         precision == RR_FP64
             ? launch_forward_j<double>(J, sub, grid, block, s, ev.before, ev.after, job, lc, g,
