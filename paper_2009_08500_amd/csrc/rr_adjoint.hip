@@ -260,21 +260,27 @@ __global__ __launch_bounds__(kBlock) void k_adj_prep(
 // With the profile gradient the FP64 subsample loop keeps each overlapping
 // subsample's separation and area in LDS (sub_lds of them per thread;
 // exposures with more, and float, where it gained only 6 %, evaluate them a
-// second time), and the weighted lerp weights go to the wave's own copy of d logL / d ldw once the exposure's
-// residual is known; the copies are stored to slot (ipv, c) of seg_gw /
-// seg_gi with flag 1 (flag 0 and nothing else if no exposure was in the
-// window), or, with seg_flag NULL (one part per vector), as the final
-// per-vector sums.
+// second time), and the weighted lerp weights go to the wave's own copy of
+// d logL / d ldw once the exposure's residual is known; the copies are stored
+// to slot (ipv, c) of seg_gw / seg_gi with flag 1 (flag 0 and nothing else if
+// no exposure was in the window), or, with seg_flag NULL (one part per vector),
+// as the final per-vector sums.
 //   use_ring 0 (tables that leave no LDS for the ring): a block's flagged
 // exposures are evaluated where they stand.
-//   Float is held to 128 vector registers (130 with the profile gradient and
-// one passband when left alone, no spills; 142 with four, five dwords spilled)
-// for four waves per SIMD: 1024 walkers x 50 000 x 5 with a profile per row and
-// its gradient 127 -> 91 us, 207 -> 165 a call; 1024 x 92 160 over four
-// passbands with the profile gradient 361 -> 257 a call.
+//   Registers: with several passbands the sums of d logL / dk and d logL /
+// d I_star, of which an exposure adds to one passband's, are kept per wave in
+// LDS (as lane sums they took 64 vector registers for up to 16 passbands).
+// FP64 then fits twice into a SIMD's registers (264 registers, once, before;
+// us per call with the profile gradient, ng 96, 1024 x 50 000: five passbands
+// nss 5 358 -> 271, eight 407 -> 318), and float four times, held to 128
+// (four passbands spilled ten before: ng 512 nss 10 345 -> 343 with two
+// passbands, 560 -> 520 with four; five at ng 96, nss 5, 303 -> 220; not held,
+// 1024 x 50 000 x 5 with a profile per row and its gradient took 207 instead
+// of 165).  Where the tables leave LDS for two workgroups a CU only, FP64 was
+// faster with one wave per SIMD (eight passbands, ng 192, nss 5: 469 -> 526).
 constexpr int kRing = 128;                    // exposures; at most 127 are held
-template <typename R, int NPBT, bool kProf>
-__global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) void k_adjoint(
+template <typename R, bool kOne, bool kProf>
+__global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 ? 4 : 2) void k_adjoint(
     const double* __restrict__ times, const int32_t* __restrict__ lcids,
     int32_t npt, LcInfo lc, const double* __restrict__ pv, int32_t npar,
     const PvConst* __restrict__ pvc, GridDev g, const R* __restrict__ T,
@@ -302,7 +308,7 @@ __global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) voi
     R* sub = reinterpret_cast<R*>(rest) + tid;
     int32_t* ring = reinterpret_cast<int32_t*>(rest + (kProf ? 2 * sizeof(R) * sub_lds * kAdjBlock : 0)) +
                     wave * kRing;
-    __shared__ double red[kWaves][kNq + NPBT];
+    __shared__ double red[kWaves][kNq + (kOne ? 1 : RR_MAX_PB)];
     __shared__ int wave_any[kWaves];
     static_assert(sizeof(red) + sizeof(wave_any) <= kAdjStaticLds,
                   "static LDS must fit the reserve the host budget assumes");
@@ -330,11 +336,10 @@ __global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) voi
 
     double ll = 0.0;
     double ga[6] = {0, 0, 0, 0, 0, 0};
-    double gk[NPBT], gi[kProf ? NPBT : 1];
-#pragma unroll
-    for (int q = 0; q < NPBT; ++q) {
-        gk[q] = 0.0;
-        if (kProf) gi[q] = 0.0;
+    double gk = 0.0, gi = 0.0;           // kOne; else red[wave] and gi_all
+    if (!kOne && lane < npb) {
+        red[wave][kNq + lane] = 0.0;
+        if (kProf) gi_all[wave * npb + lane] = 0.0;
     }
 
     for (int idx = tid; idx < npb * ng; idx += kAdjBlock) {
@@ -497,8 +502,8 @@ __global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) voi
             if (want_grad) {
 #pragma unroll
                 for (int q = 0; q < 6; ++q) ga[q] += wgt * double(gt[q]);
-#pragma unroll
-                for (int q = 0; q < NPBT; ++q) gk[q] += (q == pb) ? wgt * double(gkt) : 0.0;
+                if (kOne) gk += wgt * double(gkt);
+                else atomicAdd(&red[wave][kNq + pb], wgt * double(gkt));
             }
             if (kProf) {
                 // psi-weighted lerp weights of each overlapping subsample
@@ -531,8 +536,8 @@ __global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) voi
                     const double ip = (1.0 - al) * double(lw[m]) + al * double(lw[m + 1]);
                     git -= cw * ip * A * double(istar_inv);
                 }
-#pragma unroll
-                for (int q = 0; q < NPBT; ++q) gi[q] += (q == pb) ? git : 0.0;
+                if (kOne) gi += git;
+                else atomicAdd(&gi_all[wave * npb + pb], git);
             }
         }
     }
@@ -540,23 +545,19 @@ __global__ __launch_bounds__(kAdjBlock, sizeof(R) == 4 && NPBT <= 4 ? 4 : 1) voi
     // fixed-order reduction of the per-lane sums: butterfly within the wave,
     // then the waves in order
     if (lane == 0) wave_any[wave] = any;
-    double vals[kNq + NPBT];
+    double vals[kNq + 1];
     vals[0] = ll;
 #pragma unroll
     for (int q = 0; q < 6; ++q) vals[1 + q] = ga[q];
+    vals[kNq] = gk;
 #pragma unroll
-    for (int q = 0; q < NPBT; ++q) vals[kNq + q] = gk[q];
-#pragma unroll
-    for (int q = 0; q < kNq + NPBT; ++q) {
+    for (int q = 0; q < (kOne ? kNq + 1 : kNq); ++q) {
         const double v = wave_sum(vals[q]);
         if (lane == 0) red[wave][q] = v;
     }
-    if (kProf) {
-#pragma unroll
-        for (int q = 0; q < NPBT; ++q) {
-            const double v = wave_sum(gi[q]);
-            if (lane == 0 && q < npb) gi_all[wave * npb + q] = v;
-        }
+    if (kProf && kOne) {
+        const double v = wave_sum(gi);
+        if (lane == 0) gi_all[wave] = v;
     }
     __syncthreads();                     // also: every wave's LDS additions done
     if (tid < nq) {
@@ -885,11 +886,11 @@ __global__ __launch_bounds__(kBlock) void k_prof_grad(
 
 inline unsigned nblocks(int64_t n) { return unsigned((n + kBlock - 1) / kBlock); }
 
-template <typename R, int NPBT, bool kProf>
+template <typename R, bool kOne, bool kProf>
 void launch_adjoint_t(const AdjointArgs& A, size_t lds, hipStream_t s, const KernelEvents& ev) {
     // one part per vector: the profile sums are final and go to gldw_pv
     const bool one = A.nparts == 1;
-    launch_timed(k_adjoint<R, NPBT, kProf>, dim3(unsigned(int64_t(A.nparts) * A.npv)),
+    launch_timed(k_adjoint<R, kOne, kProf>, dim3(unsigned(int64_t(A.nparts) * A.npv)),
                  dim3(kAdjBlock), lds, s, ev.before, ev.after, A.times, A.lcids, A.npt, *A.lc,
                  A.pv, A.npar, A.pvc, A.g, static_cast<const R*>(A.T), A.inv_istar,
                  static_cast<const R*>(A.obs), A.inv_sig2, A.nblk, A.blk_lo, A.blk_hi, A.blk_ll, A.nparts,
@@ -900,14 +901,13 @@ void launch_adjoint_t(const AdjointArgs& A, size_t lds, hipStream_t s, const Ker
 
 template <typename R>
 void launch_adjoint_r(const AdjointArgs& A, size_t lds, hipStream_t s, const KernelEvents& ev) {
+    const bool one = A.g.npb == 1;
     if (A.want_prof) {
-        if (A.g.npb <= 1) launch_adjoint_t<R, 1, true>(A, lds, s, ev);
-        else if (A.g.npb <= 4) launch_adjoint_t<R, 4, true>(A, lds, s, ev);
-        else launch_adjoint_t<R, 16, true>(A, lds, s, ev);
+        if (one) launch_adjoint_t<R, true, true>(A, lds, s, ev);
+        else launch_adjoint_t<R, false, true>(A, lds, s, ev);
     } else {
-        if (A.g.npb <= 1) launch_adjoint_t<R, 1, false>(A, lds, s, ev);
-        else if (A.g.npb <= 4) launch_adjoint_t<R, 4, false>(A, lds, s, ev);
-        else launch_adjoint_t<R, 16, false>(A, lds, s, ev);
+        if (one) launch_adjoint_t<R, true, false>(A, lds, s, ev);
+        else launch_adjoint_t<R, false, false>(A, lds, s, ev);
     }
 }
 

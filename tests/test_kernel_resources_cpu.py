@@ -22,6 +22,13 @@ WAVES = {
         "k_forward_split<double, true, false>": 3,
         "k_forward_split<float, true, false>": 5,
     },
+    # <real, one passband, profile gradient>
+    "rr_adjoint.hip": {
+        **{f"k_adjoint<double, {one}, {prof}>": 2 for one in ("true", "false")
+           for prof in ("true", "false")},
+        **{f"k_adjoint<float, {one}, {prof}>": 4 for one in ("true", "false")
+           for prof in ("true", "false")},
+    },
 }
 
 
