@@ -934,12 +934,20 @@ size_t adjoint_plan_lds(int32_t precision, size_t lds_max, AdjointArgs* A) {
     lds += A->use_ring ? ring : 0;
     A->sub_lds = 0;
     if (A->want_prof && precision == RR_FP64) {
-        // as many subsamples as the largest exposure with at most kSubLds has
-        for (int l = 0; l < A->lc->nlc; ++l)
-            if (A->lc->nss[l] <= kSubLds) A->sub_lds = std::max(A->sub_lds, A->lc->nss[l]);
+        // As many subsamples as the largest exposure with at most kSubLds has,
+        // unless that halves the workgroups a CU holds (its registers allow
+        // four).  us per call, FP64, 1024 x 50 000 at nss 10, kept and evaluated
+        // again: two passbands, ng 512 (four workgroups or two) 613, 500; four,
+        // ng 512 (two, one) 1022, 1008, and 326, 272 for 100 rows; four, ng 192
+        // (four, three) 534, 522, 172 and 197; eight, ng 192 (three, two) 756, 893.
         const size_t per = 2 * elt * kAdjBlock;             // one subsample of every thread
-        const size_t left = lds + kAdjStaticLds < lds_max ? lds_max - lds - kAdjStaticLds : 0;
-        A->sub_lds = int32_t(std::min<size_t>(size_t(A->sub_lds), left / per));
+        auto resident = [&](int32_t n) {
+            return std::min<size_t>(4, lds_max / (lds + kAdjStaticLds + size_t(n) * per));
+        };
+        for (int l = 0; l < A->lc->nlc; ++l) {
+            const int32_t n = A->lc->nss[l];
+            if (n <= kSubLds && 2 * resident(n) > resident(0)) A->sub_lds = std::max(A->sub_lds, n);
+        }
         lds += size_t(A->sub_lds) * per;
     }
     return lds;

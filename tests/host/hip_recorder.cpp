@@ -1,7 +1,7 @@
 // A stand-in for the part of the HIP runtime that librr.so calls on the host,
-// preloaded by stream_memory_calls.py on a machine without a GPU: memory comes
-// from malloc, kernels are not run, and every allocation, release and launch is
-// recorded with its stream in call order.
+// preloaded by stream_memory_calls.py and loglik_plan_calls.py on a machine
+// without a GPU: memory comes from malloc, kernels are not run, and every
+// allocation, release and launch is recorded with its stream in call order.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdlib>
@@ -9,7 +9,7 @@
 #include <vector>
 
 namespace {
-struct Event { char op; hipStream_t stream; void* ptr; };
+struct Event { char op; hipStream_t stream; void* ptr; long blocks = 0, lds = 0; };
 std::vector<Event> g_log;
 char g_symbol[1 << 22];
 dim3 g_grid, g_block;                    // of the launch being made
@@ -28,6 +28,11 @@ void recorder_get(int i, char* op, void** stream, void** ptr) {
     *op = g_log[size_t(i)].op;
     *stream = g_log[size_t(i)].stream;
     *ptr = g_log[size_t(i)].ptr;
+}
+
+void recorder_launch(int i, long* blocks, long* lds) {
+    *blocks = g_log[size_t(i)].blocks;
+    *lds = g_log[size_t(i)].lds;
 }
 
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -74,8 +79,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     *s = g_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t s) {
-    g_log.push_back({'L', s, nullptr});
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3, void**, size_t lds, hipStream_t s) {
+    g_log.push_back({'L', s, nullptr, long(grid.x) * grid.y * grid.z, long(lds)});
     return hipSuccess;
 }
 }
