@@ -861,13 +861,18 @@ static int loglik_impl(const rr_tables* t, const double* times_d,
     // since more parts only cost each row more half-filled last batches (1024
     // walkers x 50 000 x 5, us per call at 2048 / 4096 / 8192 waves: float
     // 92 / 81 / 107, FP64 152 / 198 / 231; the kernel alone with the profile
-    // gradient, float 107 / 91 / -, FP64 143 / 207 / -); each wave with at
+    // gradient, float 107 / 91 / -, FP64 143 / 207 / -).  Rounded down up to 256
+    // rows, so that the last few workgroups are no second round (walkers x
+    // 50 000 x 5, rounded up / down: FP64 60 rows 51 / 44 us, 100 62 / 47, 200
+    // 82 / 64, float 100 rows 42 / 35; rows of unequal work, nss 10, FP64 100
+    // rows 96 / 103, 200 158 / 163), and up for more, where such rows would miss
+    // the finer parts (FP64 300 rows 230 / 276, 700 464 / 675).  Each wave has at
     // least 16 time blocks to look through; with the profile gradient, whose
     // parts are summed again, 2048 below 16 384 exposures (1024 walkers x 5000:
     // 75.6 us, 80.5 with 4096), at most 16 parts (64 walkers x 50 000 x 5 in
     // float: 75.5 us with 16, 81 with 25) and 256 MiB of partials.
     const int64_t waves = precision == RR_MIXED && !(prof && nblk < 256) ? 4096 : 2048;
-    int64_t nseg = (waves + 2 * int64_t(npv) - 1) / (2 * int64_t(npv));
+    int64_t nseg = (waves + (npv > 256 ? 2 * int64_t(npv) - 1 : 0)) / (2 * int64_t(npv));
     nseg = std::min<int64_t>(nseg, (int64_t(nblk) + 31) / 32);
     if (prof) {
         const size_t row_bytes = sizeof(double) * size_t(t->npb) * (size_t(g.ng) + 1);

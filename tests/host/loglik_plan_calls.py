@@ -2,7 +2,7 @@
 tests/test_loglik_plan_cpu.py in a child process with hip_recorder.cpp
 preloaded (no GPU: a device of 256 CUs with 160 KiB of LDS per workgroup).
 
-Usage: python loglik_plan_calls.py <librr.so> <path of _lib.py> lds
+Usage: python loglik_plan_calls.py <librr.so> <path of _lib.py> lds|parts
 """
 
 import ctypes
@@ -67,6 +67,18 @@ def main(lib_path, lib_py, what):
                 kept += lds > none
             L.rr_free_tables(tab)
         assert kept >= 24, kept
+    else:
+        tab = tables(1, 96)
+        for precision, waves in ((decl.RR_FP64, 2048), (decl.RR_MIXED, 4096)):
+            for profile in (False, True):
+                for npv in (60, 100, 200, 256):        # no part of a second round
+                    blocks, _ = kernel(tab, 1, npv, 50000, 5, precision, profile)
+                    # (at most one for 32 time blocks of 64, with the profile gradient 16)
+                    parts = min(waves // (2 * npv), 25, 16 if profile else 25)
+                    assert blocks == npv * parts and 2 * blocks <= waves, (npv, blocks)
+                blocks, _ = kernel(tab, 1, 300, 50000, 5, precision, profile)
+                assert blocks == 300 * -(-waves // 600), blocks
+                assert kernel(tab, 1, 5000, 50000, 5, precision, profile)[0] == 5000
     print("OK")
 
 

@@ -1,6 +1,7 @@
 """Launch of the log-likelihood kernel, on the host (tests/host/
 loglik_plan_calls.py over a recording stand-in for the HIP runtime): the
-subsamples kept in LDS never halve the workgroups that a CU holds."""
+subsamples kept in LDS never halve the workgroups that a CU holds, and few
+rows are split into no more workgroups than are resident at once."""
 
 import os
 import shutil
@@ -13,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2009_08500_amd")
 
 
-@pytest.mark.parametrize("what", ["lds"])
+@pytest.mark.parametrize("what", ["lds", "parts"])
 def test_plan(tmp_path, what):
     gxx, lib = shutil.which("g++"), os.path.join(PKG, "librr.so")
     if not gxx or not os.path.exists(lib) or not os.path.isdir("/opt/rocm/include/hip"):
