@@ -63,6 +63,17 @@ def source_hash():
 VALU_LANE_SLOTS = 256 * 4 * 16 * 2.4e9   # CUs x SIMDs x lanes x clock: wave64 takes 4 cycles
 
 
+def forward_kernel(kind, precision):
+    """(name, what a call launches) of the forward kernel that TimeSeries.kernel
+    calls `kind`."""
+    real = "double" if precision == "fp64" else "float"
+    name = {"split": "k_forward_split<%s, false, false>",
+            "split_fused": "k_forward_split<%s, true, false>",
+            "tiles": "k_forward<%s, false, 8>"}[kind] % real
+    setup = "" if kind == "split_fused" else "per-row setup + "
+    return name, "%sforward kernel '%s'" % (setup, name)
+
+
 def profile_counters(kernel):
     """Per-launch counters of `kernel` from the committed PMC summary, if it
     was taken on the current kernel sources; otherwise None."""
@@ -829,11 +840,9 @@ def main():
 
     m = summary("mixed", 4)
     d = summary("fp64", 8)
-    # the forward kernel the library launches on this series (rr_series_kernel)
-    kform = {"split": "k_forward_split<%s, false, false>", "split_fused": "k_forward_split<%s, true, false>",
-             "tiles": "k_forward<%s, false, 8>"}
-    kname = {p: kform[series.kernel(tab, npv, p)] % t
-             for p, t in (("mixed", "float"), ("fp64", "double"))}
+    # the forward kernel the library launches on this series
+    launches = {p: forward_kernel(series.kernel(tab, npv, p), p) for p in ("mixed", "fp64")}
+    kname = {p: name for p, (name, _) in launches.items()}
     achieved = m["alg_bytes"] / (m["kernel_ms"]["mean"] / 1e3) / 1e9
     kc = profile_counters(kname["mixed"])
     traffic = kc.get("hbm_bytes_per_launch") if kc else None
@@ -852,11 +861,9 @@ def main():
                              "2-min cadence, power-2 LD tabulated at 200 mu",
                     npv=npv, npt=npt, nss=nss, precision="mixed (FP64 time reduction, FP32 bulk)",
                     grid=grid,
-                    launch="one rr_evaluate_series call per step from Python (%sforward "
-                           "kernel '%s'); 'graph_replay' = the same call captured as a HIP "
-                           "graph and replayed" % (
-                               "" if kname["mixed"].endswith("true>") else "per-row setup + ",
-                               kname["mixed"])),
+                    launch="one rr_evaluate_series call per step from Python (%s); "
+                           "'graph_replay' = the same call captured as a HIP graph and "
+                           "replayed" % launches["mixed"][1]),
         graph_replay=m["graph_replay"],
         latency_ms=m["latency_ms"],
         fp64=dict(value=d["value"], ms_per_step=d["ms_per_step"], graph_replay=d["graph_replay"],
