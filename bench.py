@@ -63,11 +63,12 @@ def source_hash():
 VALU_LANE_SLOTS = 256 * 4 * 16 * 2.4e9   # CUs x SIMDs x lanes x clock: wave64 takes 4 cycles
 
 
-def forward_kernel(kind, precision):
+def forward_kernel(kind, precision, order=(False, False)):
     """(name, what a call launches) of the forward kernel that TimeSeries.kernel
-    calls `kind`."""
+    calls `kind`; a split launch with anything in TimeSeries.order is its
+    instantiation for large populations."""
     real = "double" if precision == "fp64" else "float"
-    name = {"split": "k_forward_split<%s, false, false>",
+    name = {"split": "k_forward_split<%s, false, " + ("true>" if any(order) else "false>"),
             "split_fused": "k_forward_split<%s, true, false>",
             "tiles": "k_forward<%s, false, 8>"}[kind] % real
     setup = "" if kind == "split_fused" else "per-row setup + "
@@ -841,7 +842,8 @@ def main():
     m = summary("mixed", 4)
     d = summary("fp64", 8)
     # the forward kernel the library launches on this series
-    launches = {p: forward_kernel(series.kernel(tab, npv, p), p) for p in ("mixed", "fp64")}
+    launches = {p: forward_kernel(series.kernel(tab, npv, p), p, series.order(tab, npv, p))
+                for p in ("mixed", "fp64")}
     kname = {p: name for p, (name, _) in launches.items()}
     achieved = m["alg_bytes"] / (m["kernel_ms"]["mean"] / 1e3) / 1e9
     kc = profile_counters(kname["mixed"])

@@ -228,16 +228,25 @@ RR_API int rr_evaluate_series(const rr_tables* t, const rr_series* s, const doub
  * workgroups, after the per-vector setup) or RR_KERNEL_SPLIT_FUSED (2: the
  * split launch alone, its workgroups deriving their vectors' constants
  * themselves; taken while the launch has at most 32 workgroups per CU,
- * where it measured faster, so such a call is one launch).  The two split launches give the same bits; the
- * per-tile kernel agrees with them within a rounding of the flux (see
- * rr_evaluate_series).  For benchmarks and profiles that name the kernel
- * they time.  Enqueues nothing (the choice may query the device's
- * occupancy once); errors as rr_evaluate_series's checks. */
+ * where it measured faster, so such a call is one launch).  The two split
+ * launches give the same bits; the per-tile kernel agrees with them within a
+ * rounding of the flux (see rr_evaluate_series).  For benchmarks and profiles
+ * that name the kernel they time.  Enqueues nothing (the choice may query the
+ * device's occupancy once); errors as rr_evaluate_series's checks. */
 #define RR_KERNEL_TILES 0
 #define RR_KERNEL_SPLIT 1
 #define RR_KERNEL_SPLIT_FUSED 2
 RR_API int rr_series_kernel(const rr_tables* t, const rr_series* s, int32_t npv,
                             int32_t precision, int32_t* kind);
+
+/* What the split launch of the same call does for a large population (both 0
+ * for the other kernels): *alternate = 1 if its transit and streaming
+ * workgroups alternate (else the transit workgroups come first), *bypass = 1
+ * if exposures outside every window are stored past the caches (outputs
+ * beyond 256 MB).  Neither changes a result.  Enqueues nothing; errors as
+ * rr_series_kernel. */
+RR_API int rr_series_order(const rr_tables* t, const rr_series* s, int32_t npv,
+                           int32_t precision, int32_t* alternate, int32_t* bypass);
 
 /* rr_evaluate for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, and harnesses that forbid

@@ -81,6 +81,8 @@ def _declare(L):
     L.rr_evaluate_series.restype = ctypes.c_int
     L.rr_series_kernel.argtypes = [c_void_p, c_void_p, i32, i32, c_int32_p]
     L.rr_series_kernel.restype = ctypes.c_int
+    L.rr_series_order.argtypes = [c_void_p, c_void_p, i32, i32, c_int32_p, c_int32_p]
+    L.rr_series_order.restype = ctypes.c_int
     L.rr_evaluate_ld.argtypes = [c_void_p, c_void_p, c_void_p, i32, c_void_p, c_void_p,
                                  c_void_p, i32, c_void_p, i32, i32, c_void_p, i32, c_void_p,
                                  c_void_p]

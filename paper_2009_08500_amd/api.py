@@ -190,6 +190,17 @@ class TimeSeries:
         return {_lib.RR_KERNEL_SPLIT: "split",
                 _lib.RR_KERNEL_SPLIT_FUSED: "split_fused"}.get(k.value, "tiles")
 
+    def order(self, tables, npv, precision="mixed"):
+        """(alternate, past_caches) of a "split" launch for npv rows
+        (rr_series_order): whether its transit and streaming workgroups
+        alternate, and whether exposures outside every window are stored past
+        the caches.  (False, False) for the other kernels."""
+        a, b = ctypes.c_int32(0), ctypes.c_int32(0)
+        check(_lib.lib().rr_series_order(tables.handle, self.handle, int(npv),
+                                         PRECISIONS[precision], ctypes.byref(a), ctypes.byref(b)),
+              "rr_series_order")
+        return bool(a.value), bool(b.value)
+
     def lc_args(self):
         lc = ctypes.c_void_p(self.lcids.data_ptr()) if self.lcids is not None else None
         return (lc, self.npt, _ptr(self.pbids), _ptr(self.nss), _ptr(self.exptimes), self.nlc)

@@ -572,6 +572,19 @@ RR_API int rr_series_kernel(const rr_tables* t, const rr_series* se, int32_t npv
     return RR_OK;
 }
 
+RR_API int rr_series_order(const rr_tables* t, const rr_series* se, int32_t npv,
+                           int32_t precision, int32_t* alternate, int32_t* bypass) {
+    if (!alternate || !bypass) return einval("alternate and bypass are required");
+    *alternate = *bypass = 0;
+    int32_t kind = RR_KERNEL_TILES;
+    const int rc = rr_series_kernel(t, se, npv, precision, &kind);
+    if (rc || kind != RR_KERNEL_SPLIT) return rc;
+    const SplitPlan sp = plan_forward_split(se, npv, precision);
+    *alternate = sp.run_stream > 0 ? 1 : 0;
+    *bypass = sp.bypass ? 1 : 0;
+    return RR_OK;
+}
+
 RR_API int rr_evaluate_variant(const rr_tables* t, const double* times_d,
                                const int32_t* lcids_d, int32_t npt,
                                const int32_t* pbids, const int32_t* nss,

@@ -22,9 +22,13 @@ def compiled_kernels():
 
 
 @pytest.mark.parametrize("precision", ["mixed", "fp64"])
-@pytest.mark.parametrize("kind", ["split_fused", "split", "tiles"])
-def test_launch_text(kind, precision):
-    name, text = bench.forward_kernel(kind, precision)
+@pytest.mark.parametrize("kind,order", [
+    ("split_fused", (False, False)), ("split", (False, False)), ("split", (True, False)),
+    ("split", (False, True)), ("split", (True, True)), ("tiles", (False, False))])
+def test_launch_text(kind, order, precision):
+    name, text = bench.forward_kernel(kind, precision, order)
     assert name in compiled_kernels()
+    if kind == "split":
+        assert name.endswith(", false, true>") == any(order)
     assert ("per-row setup" in text) == (kind != "split_fused")
     assert text.endswith(f"forward kernel '{name}'")
