@@ -735,6 +735,15 @@ __device__ inline const LcInfo& stage_lc(const LcInfo& lc, LcInfo* lds) {
     return *lds;
 }
 
+// Workgroups of a run of `rows` rows per tile: whole rounds of the eight XCDs,
+// so that a row's tiles stay on one XCD and its L2 (not for short runs, which
+// would idle).  300 x 5000 at nss 5 in FP64 with rows of their own 42.5 us, 47.4
+// with runs of 150 rows back to back; 2500 x 20 000 at nss 1 in float 54, with
+// runs of 63 58.5.
+__host__ __device__ inline int tile_stride(int rows) {
+    return rows >= 64 ? (rows + 7) / 8 * 8 : rows;
+}
+
 // One population (rr_evaluate): row pv0 + r, tile x of 64 J times.  kSubPar:
 // some light curve has nss > 1.  Run (y, z) of job.row_run rows, in which the
 // rows run fastest (see launch_forward).
@@ -749,9 +758,11 @@ __global__ __launch_bounds__(kFwdBlock) void k_forward(FwdJob job, LcInfo lc, Gr
     // A quotient comes out of vector registers.  Left there, the row's index and
     // all that hangs on it took 129 of them in FP64 instead of 123, so three
     // waves per SIMD instead of four (1024 x 50 000 at nss 5: 197 and 180 us).
-    const int tile = rows == 1 ? local : __builtin_amdgcn_readfirstlane(local / rows);
-    if (tile >= job.ntiles) return;
-    const int ipv = job.pv0 + r0 + (local - tile * rows);
+    const int per_tile = tile_stride(rows);
+    const int tile = per_tile == 1 ? local : __builtin_amdgcn_readfirstlane(local / per_tile);
+    const int r = local - tile * per_tile;
+    if (tile >= job.ntiles || r >= rows) return;
+    const int ipv = job.pv0 + r0 + r;
     if constexpr (kSubPar) {
         __shared__ LcInfo slc;
         forward_block<R, true, J>(job, stage_lc(lc, &slc), ipv, tile, g, T, inv_istar);
@@ -890,8 +901,9 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
     const int64_t most = waves <= 24576 ? 256 : (sub ? 1 : 64);
     const int64_t runs = (npv + most - 1) / most;
     job.row_run = int32_t((npv + runs - 1) / runs);
+    if (runs > 1 && most > 1) job.row_run = (job.row_run + 7) / 8 * 8;     // whole XCD rounds
     const int64_t gy = std::min<int64_t>(runs, 65535);
-    const dim3 grid(unsigned(int64_t(job.row_run) * job.ntiles), unsigned(gy),
+    const dim3 grid(unsigned(int64_t(tile_stride(job.row_run)) * job.ntiles), unsigned(gy),
                     unsigned((runs + gy - 1) / gy));
     const dim3 block(kFwdBlock);
     const hipError_t e =
