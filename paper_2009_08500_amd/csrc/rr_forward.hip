@@ -737,9 +737,8 @@ __device__ inline const LcInfo& stage_lc(const LcInfo& lc, LcInfo* lds) {
 
 // Workgroups of a run of `rows` rows per tile: whole rounds of the eight XCDs,
 // so that a row's tiles stay on one XCD and its L2 (not for short runs, which
-// would idle).  300 x 5000 at nss 5 in FP64 with rows of their own 42.5 us, 47.4
-// with runs of 150 rows back to back; 2500 x 20 000 at nss 1 in float 54, with
-// runs of 63 58.5.
+// would idle).  2500 x 20 000 with rows of their own in float: 54 us with runs of
+// 64 rows, 58.5 with runs of 63.
 __host__ __device__ inline int tile_stride(int rows) {
     return rows >= 64 ? (rows + 7) / 8 * 8 : rows;
 }
@@ -893,15 +892,16 @@ hipError_t launch_forward(const rr_tables* t, const double* times,
     // write more rows at a time than suits memory: 64 rows at nss 1 (512 x
     // 60 000: 38.5 -> 36.7, 64.6 -> 57.8; with 256 rows FP64 takes 66.1), and
     // row by row when supersampled, where tiles of all kinds mixed serve better
-    // (512 rows at nss 5: 38.9 and 67.1; with 64 rows 38.7 and 71.5).  The runs
-    // are of nearly equal length, one per grid row, since dividing a flat index
-    // costs every wave of a large launch (1024 x 50 000 at nss 5 in float 103,
-    // 99 us this way).
+    // (512 rows at nss 5: 38.9 and 67.1; with 64 rows 38.7 and 71.5).  Each run
+    // is a grid row, since dividing a flat index costs every wave of a large
+    // launch (1024 x 50 000 at nss 5 in float 103 us, 99 this way); the last run
+    // leaves workgroups without work, and yet runs of nearly equal length are
+    // slower (300 x 5000 at nss 5 in FP64 with rows of their own: 42 us, with 152
+    // and 148 rows 46).
     const int64_t waves = int64_t(job.ntiles) * npv;
     const int64_t most = waves <= 24576 ? 256 : (sub ? 1 : 64);
     const int64_t runs = (npv + most - 1) / most;
-    job.row_run = int32_t((npv + runs - 1) / runs);
-    if (runs > 1 && most > 1) job.row_run = (job.row_run + 7) / 8 * 8;     // whole XCD rounds
+    job.row_run = int32_t(std::min<int64_t>(npv, most));
     const int64_t gy = std::min<int64_t>(runs, 65535);
     const dim3 grid(unsigned(int64_t(tile_stride(job.row_run)) * job.ntiles), unsigned(gy),
                     unsigned((runs + gy - 1) / gy));
