@@ -125,12 +125,12 @@ template <class Ops> struct Num<float, Ops> {
 
 // sin and cos of an angle of a few radians at most: x less the nearest
 // multiple n of pi/2 (in two parts, exact in the FMA), the Maclaurin series
-// on |r| <= pi/4 -- float through r^9 and r^10 (truncation below 2e-9 of the
-// result), double through r^17 and r^18 (below 1e-19) -- and the quadrant's
+// on |r| <= pi/4 -- float through r^9 and r^10 (truncation below 2.5e-9 of the
+// result), double through r^17 and r^18 (below 1.2e-19) -- and the quadrant's
 // swap and signs.  Unlike the library's sincos it has no reduction for large
 // arguments, which made up a third of the kernels' code and cost the float
 // split kernel 13 of its 107 vector registers, so 4 resident waves of 20 per
-// CU (256 x 50 000: 21.2 -> 20.2 us; 1 x 1000 in FP64 6.6 -> 6.4).
+// CU (256 x 50 000: 21.2 -> 20.2 us; 1 x 1000 in FP64 6.16 -> 5.96).
 __host__ __device__ inline void quadrant(int n, float s0, float c0, float* s, float* c) {
     const float a = n & 1 ? c0 : s0, b = n & 1 ? s0 : c0;
     *s = n & 2 ? -a : a;
@@ -183,7 +183,7 @@ __host__ __device__ inline void sincos_near(double x, double* s, double* c) {
 // sin and cos of a half-angle x of the offset from conjunction, which is
 // small inside a transit window and below (pi + 2)/2 anywhere.  In float, for
 // |x| <= 1/4 the Maclaurin series through the x^7 and x^8 terms are summed by
-// Horner's rule in x^2 (truncation below 1e-11).
+// Horner's rule in x^2 (truncation below 1.1e-11).
 __host__ __device__ inline void sincos_small(float x, float* s, float* c) {
     if (fabsf(x) > 0.25f) {
         sincos_near(x, s, c);

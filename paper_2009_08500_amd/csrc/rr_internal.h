@@ -255,7 +255,8 @@ size_t adjoint_plan_lds(int32_t precision, size_t lds_max, AdjointArgs* a);
 // What the log-likelihood kernel declares in LDS statically (an upper
 // bound): the dynamic part must fit in lds_max less this.
 constexpr size_t kAdjStaticLds = 512;
-// Per-row constants (launch_pv_setup_k's), time-block bounds and sums.
+// Per-row constants (as launch_pv_setup; k in [k_lo, k_hi], or in (0, k_small)
+// for small-planet rows), time-block bounds and sums.
 hipError_t launch_adjoint_prep(const AdjointArgs& a, int32_t precision, double k_lo, double k_hi,
                                double k_small, hipStream_t s);
 hipError_t launch_adjoint(const AdjointArgs& a, size_t lds, int32_t precision, hipStream_t s);

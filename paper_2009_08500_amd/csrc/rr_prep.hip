@@ -610,9 +610,9 @@ __global__ __launch_bounds__(kBlock, 3) void k_pv_tables(const WT* __restrict__ 
 // those that need not be, 55 without the nodes no exposure reads either (a third
 // of them, but the cheap ones near the centre).
 constexpr int kDirectWaves = 4;            // 66 / 59 / 63 us with 2 / 4 / 8
-// sqrt of a normal x > 0 from the hardware's reciprocal square root and two
-// refinements: within an ulp or two, without the library's scaling and its
-// last rounding step.
+// sqrt of a normal x > 0 by Goldschmidt's iteration: s -> sqrt x and h ->
+// 1 / (2 sqrt x) from the hardware's reciprocal square root, refined once
+// together, then s once more by its residual; within an ulp or two.
 __device__ inline double sqrt_nr(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     double s = x * y, h = 0.5 * y;
