@@ -5,9 +5,9 @@ Workload: the population evaluation: 512 parameter vectors drawn from a
 fixed seed (k ~ U(0.05, 0.2), a ~ U(5, 20), b ~ U(0, 0.9), e ~ U(0, 0.3),
 w ~ U(0, 2 pi), P ~ U(1, 10) d, t0 ~ U(0, P)) over 20 000 times at 2-min
 cadence (27.8 d), one power-2 limb-darkening profile tabulated at 200 mu,
-no supersampling, default table grid.  One step is one rr_evaluate call
-(per-vector setup kernel + forward kernel) over the whole population with
-inputs and tables resident in HBM.  The mixed-precision path (FP64 time
+no supersampling, default table grid.  One step is one rr_evaluate_series
+call (one fused launch at this size) over the whole population with inputs
+and tables resident in HBM.  The mixed-precision path (FP64 time
 reduction, FP32 bulk) gives the headline value; the FP64 path is timed the
 same way and reported beside it.
 

@@ -507,8 +507,8 @@ __device__ inline void pv_tables_mfma_ordered(const double* __restrict__ W,
 // flight only have to keep that busy (float 18.2 us with 40 of them).  In FP64
 // a wave takes one of the two table rows, so that few rows still keep enough
 // loads in flight (a call of 37 rows x 5000 32 us with both, 26 with one; 512 x
-// 20 000 78 and 77, 75 with the bins split over four waves, whose order is
-// another).
+// 20 000 78 and 76; with the bins split over four waves, whose order is another,
+// 25 and 73, and 1024 x 1000 103 instead of 112).
 template <typename WT>
 constexpr int kRowTabs = sizeof(WT) == 4 ? 2 : 1;                 // table rows per wave
 template <typename WT>
