@@ -76,6 +76,18 @@ static int check_grid(const rr_grid* g) {
 // nothing is kept for it.
 static bool keeps_buffers(hipStream_t stream) { return stream != hipStreamPerThread; }
 
+using KeptBuffers = std::unordered_map<hipStream_t, std::pair<void*, size_t>>;
+
+// The stream's entry, a new one {nullptr, 0}; NULL if there is no memory for it
+// (nothing may throw through the C interface).
+static std::pair<void*, size_t>* kept_buffer(KeptBuffers* m, hipStream_t stream) {
+    try {
+        return &(*m)[stream];
+    } catch (const std::bad_alloc&) {
+        return nullptr;
+    }
+}
+
 // Memory of one call from the stream-ordered allocator, given back behind the
 // work that the call has enqueued.
 class StreamMemory {
@@ -105,7 +117,9 @@ static hipError_t stream_workspace(rr_tables* t, hipStream_t stream, size_t byte
                                    StreamMemory* own, void** out) {
     if (!keeps_buffers(stream)) return own->alloc(stream, bytes, out);
     std::lock_guard<std::mutex> lk(t->ws_mu);
-    auto& slot = t->ws[stream];
+    auto* kept = kept_buffer(&t->ws, stream);
+    if (!kept) return hipErrorOutOfMemory;
+    auto& slot = *kept;
     if (slot.second < bytes) {
         if (slot.first) {
             hipError_t e = hipFree(slot.first);     // synchronising; growth only
@@ -144,7 +158,9 @@ class CallMemory {
         if (cap == hipStreamCaptureStatusNone && bytes <= kKeepBytes && keeps_buffers(stream)) {
             lk_ = std::unique_lock<std::mutex>(t->lk_mu);
             const bool again = t->lk.count(stream) != 0;    // a first call keeps nothing
-            auto& slot = t->lk[stream];
+            auto* kept = kept_buffer(&t->lk, stream);
+            if (!kept) return hipErrorOutOfMemory;
+            auto& slot = *kept;
             if (again && slot.second < bytes && t->lk_total - slot.second + bytes <= kKeepTotal) {
                 // stream-ordered too: the buffer that is given up may be in use
                 const size_t nb = std::min(kKeepBytes, std::max(bytes, size_t(1) << 16));

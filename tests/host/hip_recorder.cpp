@@ -5,7 +5,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <cstdlib>
-#include <cstring>
+#include <new>
 #include <vector>
 
 namespace {
@@ -15,6 +15,7 @@ char g_symbol[1 << 22];
 dim3 g_grid, g_block;                    // of the launch being made
 size_t g_lds;
 hipStream_t g_stream;
+bool g_no_memory = false;                // operator new throws
 hipError_t allocate(char op, void** p, size_t n, hipStream_t s) {
     *p = std::malloc(n);
     g_log.push_back({op, s, *p});
@@ -22,7 +23,19 @@ hipError_t allocate(char op, void** p, size_t n, hipStream_t s) {
 }
 }  // namespace
 
+void* operator new(std::size_t n) {
+    void* p = g_no_memory ? nullptr : std::malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+
 extern "C" {
+void recorder_no_memory(int on) {
+    g_log.reserve(g_log.size() + 64);    // what is recorded meanwhile has its place
+    g_no_memory = on != 0;
+}
 int recorder_size() { return int(g_log.size()); }
 void recorder_get(int i, char* op, void** stream, void** ptr) {
     *op = g_log[size_t(i)].op;

@@ -74,6 +74,15 @@ def main(lib_path, lib_py):
                     assert ev[0][1] == stream, (name, k, ev)
                 elif k > 1:
                     assert not mem, (name, k, ev)           # a kept buffer
+        # no host memory for a new stream's entry: an error code, and nothing enqueued
+        first = rec.recorder_size()
+        rec.recorder_no_memory(1)
+        rc = call(ctypes.c_void_p(0x2000))
+        rec.recorder_no_memory(0)
+        assert rc == decl.RR_ENOMEM and not log(first), (name, rc, log(first))
+        assert call(ctypes.c_void_p(0x2000)) == 0, name
+        L.rr_free_tables(tab)
+        assert L.rr_prepare_ld(p(mu), p(prof), 20, 1, ctypes.byref(grid), ctypes.byref(tab)) == 0
         print(name)
     L.rr_free_tables(tab)
     L.rr_series_free(ser)

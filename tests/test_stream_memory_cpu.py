@@ -1,5 +1,6 @@
 """A call's temporaries by stream handle, on the host: on hipStreamPerThread,
-one handle for a different stream in every thread, no buffer outlives its call
+one handle for a different stream in every thread, no buffer outlives its call;
+and without host memory for a new stream's entry a call returns RR_ENOMEM
 (tests/host/stream_memory_calls.py over a recording stand-in for the HIP
 runtime)."""
 
